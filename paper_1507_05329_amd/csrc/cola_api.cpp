@@ -19,8 +19,7 @@ using namespace cola;
 
 namespace {
 
-constexpr int kMaxBins = 4096;
-constexpr int kPkChunks = 64;
+constexpr int kMaxBins = kPkMaxBins;
 const double kPi = 3.14159265358979323846;
 
 size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
@@ -100,7 +99,7 @@ Layout layout(const cola_params* p) {
   L.mesh = take(L.mesh_region * sizeof(float2));
   L.tw = take(4 * (size_t)L.tw_cap * sizeof(float2));
   L.amp = take(L.amp_len * sizeof(float));
-  L.pk_partial = take((size_t)kMaxBins * kPkChunks * 3 * sizeof(double));
+  L.pk_partial = take((size_t)kPkPartialDoubles * sizeof(double));
   L.pk_out = take((size_t)kMaxBins * 3 * sizeof(double));
   L.pk_edges = take((size_t)(kMaxBins + 1) * sizeof(double));
   L.flag = take(sizeof(uint32_t) * 64);
@@ -655,8 +654,7 @@ int pk_of(cola_ctx* c, const float* disp, int32_t ng, const double* edges, int32
   float2* m = c->mesh[0];
   deposit(c, ng, reinterpret_cast<float*>(m), 2 * padded_cols(ng), 1, disp);
   fft3d_forward(m, ng, c->tw, c->stream);
-  launch_pk_bin(m, ng, c->p.box, c->pk_edges, nbins, c->pk_partial, kPkChunks, c->stream);
-  launch_pk_reduce(c->pk_partial, nbins, kPkChunks, c->pk_out, c->stream);
+  launch_pk_bin(m, ng, c->p.box, c->pk_edges, nbins, c->pk_partial, kPkChunks, c->pk_out, c->stream);
   LAUNCH_CHECK(c, "cola_pk");
   std::vector<double> h(3 * (size_t)nbins);
   HIP_TRY(c, hipMemcpyAsync(h.data(), c->pk_out, h.size() * sizeof(double), hipMemcpyDeviceToHost,
@@ -709,8 +707,7 @@ int pk_jing_of(cola_ctx* c, const float* disp, int32_t ng, const double* edges, 
   float2* m = c->mesh[0];
   deposit(c, ng, reinterpret_cast<float*>(m), 2 * padded_cols(ng), 1, disp);
   fft3d_forward(m, ng, c->tw, c->stream);
-  launch_pk_bin(m, ng, c->p.box, c->pk_edges, nbins, c->pk_partial, kPkChunks, c->stream, 0);
-  launch_pk_reduce(c->pk_partial, nbins, kPkChunks, c->pk_out, c->stream);
+  launch_pk_bin(m, ng, c->p.box, c->pk_edges, nbins, c->pk_partial, kPkChunks, c->pk_out, c->stream, 0);
   LAUNCH_CHECK(c, "cola_pk_jing");
   std::vector<double> h(3 * (size_t)nbins);
   HIP_TRY(c, hipMemcpyAsync(h.data(), c->pk_out, h.size() * sizeof(double), hipMemcpyDeviceToHost,
@@ -1044,9 +1041,7 @@ int cola_pk_adjoint(cola_ctx* c, const float* disp, int32_t ng, const double* ed
   float2* Z = c->mesh[1];
   deposit(c, ng, reinterpret_cast<float*>(X), rs, 1, disp);
   fft3d_forward(X, ng, c->tw, c->stream);
-  launch_pk_bin(X, ng, c->p.box, c->pk_edges, nbins, c->pk_partial, kPkChunks, c->stream);
-  launch_pk_reduce(c->pk_partial, nbins, kPkChunks, c->pk_out, c->stream);
-  launch_fill_u32(reinterpret_cast<uint32_t*>(Z), 2 * mesh_complex_count(ng), 0u, c->stream);
+  launch_pk_bin(X, ng, c->p.box, c->pk_edges, nbins, c->pk_partial, kPkChunks, c->pk_out, c->stream);
   launch_pk_adj_modes(X, Z, ng, c->p.box, c->pk_edges, nbins, c->pk_cbar, c->pk_out, c->stream);
   fft3d_inverse(Z, ng, c->tw, c->stream);
   const float dscale = (float)((double)ng / (double)c->p.nmesh);

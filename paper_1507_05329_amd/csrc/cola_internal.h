@@ -195,12 +195,14 @@ void launch_init_particles(float* disp, float* vres, const float* psi1, const fl
                            long np3, float D1, float D2, hipStream_t s);
 void launch_axpby(float* y, const float* x, float a, float b, long n, hipStream_t s);
 // Power spectrum binning (k_pk.hip).
+// partial: kPkPartialDoubles doubles; out: sum |k|, sum P and the count per bin.
+constexpr int kPkMaxBins = 4096, kPkChunks = 64;
+constexpr long kPkPartialDoubles = 3L * kPkMaxBins * kPkChunks;
 void launch_pk_bin(const float2* spec, int ng, double box, const double* edges, int nbins,
-                   double* partial, int nchunk, hipStream_t s, int deconvolve = 1);
+                   double* partial, int nchunk, double* out, hipStream_t s, int deconvolve = 1);
 // Jing (2005) image sums of the CIC window per bin at the per-bin slopes (out: nbins sums).
 void launch_pk_alias(int ng, double box, const double* edges, int nbins, const double* slope, double* partial,
                      int nchunk, double* out, hipStream_t s);
-void launch_pk_reduce(const double* partial, int nbins, int nchunk, double* out, hipStream_t s);
 // Density / line-of-sight momentum spectra: partial holds 5 doubles per (bin, chunk),
 // out 5 per bin (sum |k|, P_dd, P_du, P_uu, count).
 void launch_pk_cross(const float2* sd, const float2* sp, int ng, double box, const double* edges, int nbins,

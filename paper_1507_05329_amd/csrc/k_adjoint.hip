@@ -172,64 +172,4 @@ void launch_phibar_off(float* a, const float* sbar, int n, long row_stride, long
                      row_stride, mesh_stride_floats);
 }
 
-// P(k) adjoint: for half-space modes with |k| <= k_Nyq in bin b,
-//   u_k = cbar_b / N_b (V/Ng^3)^2 / V / W_CIC(k)^2,
-// and the real field  deltabar(x) = sum_modes 2 u_k Re(X_k e^{ikx})  is written
-// as a half spectrum Z for the unnormalised complex-to-real inverse:
-//   0 < nz < Ng/2: Z_k = u X_k (the inverse doubles it);  nz = 0: Z_k = u X_k and
-//   Z_{-k} = conj(u X_k) (Hermitian plane);  nz = Ng/2: Z_k = 2 u X_k.
-__device__ __forceinline__ double sinc_pi_d(double x) {
-  if (x == 0.0) return 1.0;
-  const double a = 3.14159265358979323846 * x;
-  return sin(a) / a;
-}
-
-__global__ void k_pk_adj_modes(const float2* __restrict__ X, float2* __restrict__ Z, int ng, long cols,
-                               double kf, double kmax, double vol_fac,
-                               const double* __restrict__ edges, int nbins,
-                               const double* __restrict__ cbar, const double* __restrict__ sums) {
-  const int h = ng / 2;
-  const long nmode = (long)ng * ng * (h + 1);
-  for (long m = blockIdx.x * (long)blockDim.x + threadIdx.x; m < nmode; m += (long)gridDim.x * blockDim.x) {
-    const int iz = (int)(m % (h + 1));
-    const long r = m / (h + 1);
-    const int ix = (int)(r / ng), iy = (int)(r % ng);
-    const int nx = ix < h ? ix : ix - ng, ny = iy < h ? iy : iy - ng, nz = iz;
-    if (nz == 0 && !(ny > 0 || (ny == 0 && nx > 0))) continue;
-    const double n2 = (double)nx * nx + (double)ny * ny + (double)nz * nz;
-    const double kk = kf * sqrt(n2);
-    if (kk > kmax) continue;
-    // bin: last edge <= kk
-    if (!(kk >= edges[0] && kk < edges[nbins])) continue;
-    int lo = 0, hi = nbins;  // edges[0..nbins]
-    while (hi - lo > 1) {
-      const int mid = (lo + hi) / 2;
-      if (edges[mid] <= kk) lo = mid; else hi = mid;
-    }
-    const double cnt = sums[3 * lo + 2];
-    if (cnt <= 0) continue;
-    double w = sinc_pi_d((double)nx / ng) * sinc_pi_d((double)ny / ng) * sinc_pi_d((double)nz / ng);
-    w = w * w;
-    const double u = cbar[lo] / cnt * vol_fac / (w * w);
-    const float2 x = X[r * cols + iz];
-    const double fac = (nz == h) ? 2.0 * u : u;
-    Z[r * cols + iz] = make_float2((float)(fac * x.x), (float)(fac * x.y));
-    if (nz == 0) {
-      const int jx = (ng - ix) % ng, jy = (ng - iy) % ng;
-      Z[((long)jx * ng + jy) * cols] = make_float2((float)(u * x.x), (float)(-u * x.y));
-    }
-  }
-}
-
-void launch_pk_adj_modes(const float2* X, float2* Z, int ng, double box, const double* edges,
-                         int nbins, const double* cbar, const double* sums, hipStream_t s) {
-  const double pi = 3.14159265358979323846;
-  const double kf = 2.0 * pi / box, kmax = pi * ng / box;
-  const double v = box * box * box, n3 = (double)ng * ng * ng;
-  const double vol_fac = (v / n3) * (v / n3) / v;
-  const long nmode = (long)ng * ng * (ng / 2 + 1);
-  hipLaunchKernelGGL(k_pk_adj_modes, dim3(grid_1d(nmode)), dim3(256), 0, s, X, Z, ng,
-                     padded_cols(ng), kf, kmax, vol_fac, edges, nbins, cbar, sums);
-}
-
 }  // namespace cola

@@ -3,8 +3,8 @@
 // delta_k = (V / Ng^3) DFT[delta] / W_CIC(k), W_CIC = prod sinc^2(pi n_e / Ng),
 // averaged per |k| bin with the mean |k|.  Only |k| <= pi Ng / L is used.
 //
-// Deterministic reduction: workgroup (bin b, chunk c) visits the (kx, ky)
-// rows of chunk c; a thread walks one row's kz range that can fall in bin b
+// Up to 512 bins: k_pk_rows below.  More bins: workgroup (bin b, chunk c)
+// visits the (kx, ky) rows of chunk c; a thread walks one row's kz range that can fall in bin b
 // (found analytically, each mode then tested exactly), accumulating in FP64
 // in a fixed order; the workgroup sums its threads by a fixed tree, and a
 // second kernel sums the chunks in order.
@@ -169,6 +169,277 @@ __global__ void k_pk_cross_reduce(const double* __restrict__ partial, int nbins,
   for (int q = 0; q < 5; ++q) out[5 * b + q] = s[q];
 }
 
+// ---------------------------------------------------------------------------
+// Spectra of few bins (kRowBins at most), one pass over the modes.  The sums
+// by (bin, chunk) above visit every (kx, ky) row once per bin and take two
+// sines per visited mode; here a wave visits each mode of its rows once, and
+// the windows come from a table in LDS.  What bounds it is the FP64 arithmetic
+// of a mode (a square root and the window).  768 mesh: 0.7 ms at 1 and 8 bins,
+// 0.8 at 40, 1.6 at 512, against 5.4, 5.8, 3.4 and 2.9 ms with the sums by
+// (bin, chunk), which remain for more bins (their LDS sums no longer fit).
+//
+// Bins by integers: n2 = nx^2 + ny^2 + nz^2 decides |k| = kf sqrt(n2), so bin b
+// is thr[b] <= n2 < thr[b + 1] with thr[b] the smallest n2 whose |k| reaches
+// edge b (same expression, same rounding), and |k| <= kmax is n2 < top.
+// A lane keeps one nz and goes through the rows, along which n2 changes
+// little, so it adds into registers and passes its sums on only when its bin
+// changes, to LDS sums that belong to its wave alone.  A wave's additions
+// come in program order, the lanes of one of them in lane order, and the
+// waves and chunks are added in order: the sums do not vary from run to run.
+constexpr int kRowBins = 512;        // largest bin count: LDS of a workgroup, chunks that the partials hold
+constexpr int kRowWaves = 4;
+constexpr int kRowMaxChunks = 1024;  // workgroups
+
+__device__ __forceinline__ uint32_t first_n2(double e, double kf, bool strict) {
+  // smallest integer n2 >= 0 with kf sqrt(n2) >= e (strict: > e); 2^24 where there is none below
+  const double q = e / kf;
+  if (!(q > 0.0)) return strict && q == 0.0 ? 1u : 0u;
+  const double q2 = q * q;
+  if (!(q2 < 16777216.0)) return 16777216u;
+  uint32_t n = (uint32_t)q2;
+  n = n > 2u ? n - 2u : 0u;
+  for (;; ++n) {
+    const double k = kf * sqrt((double)n);
+    if (strict ? k > e : k >= e) return n;
+  }
+}
+
+// NS sums per bin and the mode count.  CROSS: |k|, |d|^2, sign(n_axis) Im(d p*),
+// |p|^2; otherwise |k|, |d|^2.
+template <bool CROSS>
+__global__ __launch_bounds__(64 * kRowWaves) void k_pk_rows(
+    const float2* __restrict__ sd, const float2* __restrict__ sp, int ng, long cols, double kf, double kmax,
+    double vol_fac, const double* __restrict__ edges, int nbins, int axis, double* __restrict__ partial,
+    int nchunk, int deconvolve) {
+  constexpr int NS = CROSS ? 4 : 2, T = 64 * kRowWaves, kU = 4;
+  extern __shared__ double smem[];
+  double* acc = smem;                                        // [wave][bin][NS]
+  double* win = acc + (size_t)kRowWaves * nbins * NS;        // 1 / sinc^4 per axis index
+  uint32_t* thr = reinterpret_cast<uint32_t*>(win + ng / 2 + 1);  // nbins + 1
+  uint32_t* cnt = thr + nbins + 1;                           // [wave][bin]
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int h = ng / 2;
+  for (int i = tid; i < kRowWaves * nbins * NS; i += T) acc[i] = 0.0;
+  for (int i = tid; i < kRowWaves * nbins; i += T) cnt[i] = 0u;
+  for (int i = tid; i <= h; i += T) {
+    const double s = deconvolve ? sinc_pi((double)i / ng) : 1.0;
+    win[i] = 1.0 / ((s * s) * (s * s));
+  }
+  for (int i = tid; i <= nbins; i += T) thr[i] = first_n2(edges[i], kf, false);
+  const uint32_t top = first_n2(kmax, kf, true);
+  __syncthreads();
+  const uint32_t lo = thr[0], hi = min(thr[nbins], top);
+  double* wacc = acc + (size_t)wave * nbins * NS;
+  uint32_t* wcnt = cnt + wave * nbins;
+
+  double run[NS];                                            // the lane's sums of bin cur
+#pragma unroll
+  for (int q = 0; q < NS; ++q) run[q] = 0.0;
+  uint32_t nrun = 0, tlo, thi;                               // bin cur: tlo <= n2 < thi
+  int cur;
+  auto flush = [&]() {
+    if (nrun > 0) {
+#pragma unroll
+      for (int q = 0; q < NS; ++q) {
+        __hip_atomic_fetch_add(&wacc[cur * NS + q], run[q], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        run[q] = 0.0;
+      }
+      atomicAdd(&wcnt[cur], nrun);
+      nrun = 0;
+    }
+  };
+
+  const int nrows = ng * ng, nw = nchunk * kRowWaves;
+  const int gw = (int)blockIdx.x * kRowWaves + wave;
+  const int per = (nrows + nw - 1) / nw;
+  const int r0 = min(gw * per, nrows), r1 = min(r0 + per, nrows);
+  for (int z0 = 0; z0 <= h; z0 += 64) {
+    const int nz = z0 + lane;
+    const bool zin = nz <= h;
+    const double wz = win[zin ? nz : h];
+    cur = -1;
+    tlo = 1u;
+    thi = 0u;
+    for (int rb = r0; rb < r1; rb += kU) {
+      float2 d[kU], p[kU];
+      uint32_t p2[kU];
+      int sx[kU], sy[kU];
+#pragma unroll
+      for (int u = 0; u < kU; ++u) {
+        const int r = min(rb + u, nrows - 1);
+        const int ix = r / ng, iy = r - ix * ng;
+        sx[u] = ix < h ? ix : ix - ng;
+        sy[u] = iy < h ? iy : iy - ng;
+        p2[u] = rb + u < r1 ? (uint32_t)(sx[u] * sx[u] + sy[u] * sy[u]) : 16777216u;
+        const bool in = zin && p2[u] + (uint32_t)(z0 * z0) < hi;
+        d[u] = in ? sd[(long)r * cols + nz] : make_float2(0.f, 0.f);
+        if constexpr (CROSS) p[u] = in ? sp[(long)r * cols + nz] : make_float2(0.f, 0.f);
+      }
+#pragma unroll
+      for (int u = 0; u < kU; ++u) {
+        if (p2[u] + (uint32_t)(z0 * z0) >= hi) continue;     // wave-uniform: nothing of the row is left
+        const uint32_t n2 = p2[u] + (uint32_t)(nz * nz);
+        if (!(zin && n2 >= lo && n2 < hi && (nz > 0 || sy[u] > 0 || (sy[u] == 0 && sx[u] > 0)))) continue;
+        if (n2 < tlo || n2 >= thi) {
+          flush();
+          if (cur < 0) {                                     // the last edge not above n2
+            int a = 0, e = nbins;
+            while (e - a > 1) {
+              const int m = (a + e) >> 1;
+              if (thr[m] <= n2) a = m; else e = m;
+            }
+            cur = a;
+          } else {                                           // mostly the next bin or the one before
+            while (thr[cur + 1] <= n2) ++cur;
+            while (thr[cur] > n2) --cur;
+          }
+          tlo = thr[cur];
+          thi = thr[cur + 1];
+        }
+        const double f = vol_fac * (win[abs(sx[u])] * win[abs(sy[u])] * wz);
+        const double dr = d[u].x, di = d[u].y;
+        run[0] += kf * sqrt((double)n2);
+        run[1] += (dr * dr + di * di) * f;
+        if constexpr (CROSS) {
+          const double pr = p[u].x, pi = p[u].y;
+          const int na = axis == 0 ? sx[u] : axis == 1 ? sy[u] : nz;
+          run[2] += (na > 0 ? 1.0 : na < 0 ? -1.0 : 0.0) * (di * pr - dr * pi) * f;
+          run[3] += (pr * pr + pi * pi) * f;
+        }
+        ++nrun;
+      }
+    }
+    flush();
+  }
+  __syncthreads();
+  for (int b = tid; b < nbins; b += T) {
+    double s[NS + 1];
+    for (int q = 0; q <= NS; ++q) s[q] = 0.0;
+    for (int w = 0; w < kRowWaves; ++w) {
+      for (int q = 0; q < NS; ++q) s[q] += acc[((size_t)w * nbins + b) * NS + q];
+      s[NS] += (double)cnt[w * nbins + b];
+    }
+    double* o = partial + ((long)b * nchunk + blockIdx.x) * (NS + 1);
+    for (int q = 0; q <= NS; ++q) o[q] = s[q];
+  }
+}
+
+// Sums the chunks of a bin: one workgroup per bin, strided partial sums and a
+// fixed tree.
+template <int NV>
+__global__ __launch_bounds__(256) void k_pk_rows_reduce(const double* __restrict__ partial, int nchunk,
+                                                        double* __restrict__ out) {
+  __shared__ double s[NV][256];
+  const int b = blockIdx.x, t = threadIdx.x;
+  double a[NV];
+#pragma unroll
+  for (int q = 0; q < NV; ++q) a[q] = 0.0;
+  for (int c = t; c < nchunk; c += 256)
+#pragma unroll
+    for (int q = 0; q < NV; ++q) a[q] += partial[((long)b * nchunk + c) * NV + q];
+#pragma unroll
+  for (int q = 0; q < NV; ++q) s[q][t] = a[q];
+  __syncthreads();
+  for (int o = 128; o > 0; o >>= 1) {
+    if (t < o)
+#pragma unroll
+      for (int q = 0; q < NV; ++q) s[q][t] += s[q][t + o];
+    __syncthreads();
+  }
+  if (t < NV) out[(long)b * NV + t] = s[t][0];
+}
+
+namespace {
+size_t pk_rows_lds(int ng, int nbins, int ns) {
+  return sizeof(double) * ((size_t)kRowWaves * nbins * ns + ng / 2 + 1) +
+         sizeof(uint32_t) * (nbins + 1 + (size_t)kRowWaves * nbins);
+}
+// Whether the row kernel serves nbins bins of nv sums (64 KB of LDS at most),
+// and its chunks: at least 16 rows per wave, at most what the partials (cap
+// doubles) hold.
+bool pk_rows_plan(int ng, int nbins, int nv, long cap, int* nchunk) {
+  if (nbins > kRowBins || pk_rows_lds(ng, nbins, nv - 1) > 65536) return false;
+  long n = (long)ng * ng / (16 * kRowWaves);
+  n = n < kRowMaxChunks ? n : kRowMaxChunks;
+  const long fit = cap / ((long)nbins * nv);
+  *nchunk = (int)(n < fit ? (n > 0 ? n : 1) : fit);
+  return true;
+}
+}  // namespace
+
+// P(k) adjoint: for half-space modes with |k| <= k_Nyq in bin b,
+//   u_k = cbar_b / N_b (V/Ng^3)^2 / V / W_CIC(k)^2,
+// and the real field  deltabar(x) = sum_modes 2 u_k Re(X_k e^{ikx})  is written
+// as a half spectrum Z for the unnormalised complex-to-real inverse:
+//   0 < nz < Ng/2: Z_k = u X_k (the inverse doubles it);  nz = 0: Z_k = u X_k and
+//   Z_{-k} = conj(u X_k) (Hermitian plane);  nz = Ng/2: Z_k = 2 u X_k.
+// A wave takes whole rows, lanes along nz, and writes every value of Z (zero
+// where no bin counts the mode, and in the row padding); bins and windows as
+// in k_pk_rows.  An element of the nz = 0 plane outside the half space takes
+// its value from its conjugate partner.
+__global__ __launch_bounds__(64 * kRowWaves) void k_pk_adj_rows(
+    const float2* __restrict__ X, float2* __restrict__ Z, int ng, int cols, double kf, double kmax, double vol_fac,
+    const double* __restrict__ edges, int nbins, const double* __restrict__ cbar, const double* __restrict__ sums) {
+  extern __shared__ double smem[];
+  double* win = smem;
+  double* cb = win + ng / 2 + 1;
+  uint32_t* thr = reinterpret_cast<uint32_t*>(cb + nbins);
+  const int tid = threadIdx.x, lane = tid & 63, h = ng / 2;
+  for (int i = tid; i <= h; i += 64 * kRowWaves) {
+    const double s = sinc_pi((double)i / ng);
+    win[i] = 1.0 / ((s * s) * (s * s));
+  }
+  for (int i = tid; i < nbins; i += 64 * kRowWaves) {
+    const double n = sums[3 * i + 2];
+    cb[i] = n > 0 ? cbar[i] / n * vol_fac : 0.0;
+  }
+  for (int i = tid; i <= nbins; i += 64 * kRowWaves) thr[i] = first_n2(edges[i], kf, false);
+  const uint32_t top = first_n2(kmax, kf, true);
+  __syncthreads();
+  const uint32_t lo = thr[0], hi = min(thr[nbins], top);
+  const int nrows = ng * ng, nw = (int)gridDim.x * kRowWaves;
+  for (int r = (int)blockIdx.x * kRowWaves + (tid >> 6); r < nrows; r += nw) {
+    const int ix = r / ng, iy = r - ix * ng;
+    const int nx = ix < h ? ix : ix - ng, ny = iy < h ? iy : iy - ng;
+    const uint32_t p2 = (uint32_t)(nx * nx + ny * ny);
+    const double wxy = win[abs(nx)] * win[abs(ny)];
+    for (int nz = lane; nz < cols; nz += 64) {
+      float2 z = make_float2(0.f, 0.f);
+      const uint32_t n2 = p2 + (uint32_t)(nz * nz);
+      if (nz <= h && n2 >= lo && n2 < hi && n2 > 0) {
+        // outside the half space: the partner (-nx, -ny), unless that is outside too
+        const bool in = nz > 0 || ny > 0 || (ny == 0 && nx > 0);
+        const int jx = (ng - ix) % ng, jy = (ng - iy) % ng;
+        const int mx = jx < h ? jx : jx - ng, my = jy < h ? jy : jy - ng;
+        if (in || my > 0 || (my == 0 && mx > 0)) {
+          int a = 0, e = nbins;
+          while (e - a > 1) {
+            const int m = (a + e) >> 1;
+            if (thr[m] <= n2) a = m; else e = m;
+          }
+          const double u = cb[a] * (wxy * win[nz]) * (nz == h ? 2.0 : 1.0);
+          const float2 x = in ? X[(long)r * cols + nz] : X[((long)jx * ng + jy) * cols];
+          z = make_float2((float)(u * x.x), (float)((in ? u : -u) * x.y));
+        }
+      }
+      Z[(long)r * cols + nz] = z;
+    }
+  }
+}
+
+void launch_pk_adj_modes(const float2* X, float2* Z, int ng, double box, const double* edges,
+                         int nbins, const double* cbar, const double* sums, hipStream_t s) {
+  const double pi = 3.14159265358979323846;
+  const double kf = 2.0 * pi / box, kmax = pi * ng / box;
+  const double v = box * box * box, n3 = (double)ng * ng * ng;
+  const double vol_fac = (v / n3) * (v / n3) / v;
+  const int rows = ng * ng;
+  const unsigned blocks = (unsigned)(rows / (8 * kRowWaves) < 4096 ? rows / (8 * kRowWaves) : 4096);
+  const size_t lds = sizeof(double) * (ng / 2 + 1 + nbins) + sizeof(uint32_t) * (nbins + 1);
+  hipLaunchKernelGGL(k_pk_adj_rows, dim3(blocks), dim3(64 * kRowWaves), lds, s, X, Z, ng, (int)padded_cols(ng), kf,
+                     kmax, vol_fac, edges, nbins, cbar, sums);
+}
+
 void launch_pk_cross(const float2* sd, const float2* sp, int ng, double box, const double* edges, int nbins,
                      int axis, double* partial, int nchunk, double* out, hipStream_t s) {
   const double pi = 3.14159265358979323846;
@@ -177,22 +448,39 @@ void launch_pk_cross(const float2* sd, const float2* sp, int ng, double box, con
   const double v = box * box * box;
   const double n3 = (double)ng * ng * ng;
   const double vol_fac = (v / n3) * (v / n3) / v;
+  int nc = 0;
+  if (pk_rows_plan(ng, nbins, 5, kPkPartialDoubles, &nc)) {
+    hipLaunchKernelGGL(k_pk_rows<true>, dim3((unsigned)nc), dim3(64 * kRowWaves), pk_rows_lds(ng, nbins, 4), s, sd, sp,
+                       ng, padded_cols(ng), kf, kmax, vol_fac, edges, nbins, axis, partial, nc, 1);
+    hipLaunchKernelGGL(k_pk_rows_reduce<5>, dim3((unsigned)nbins), dim3(256), 0, s, partial, nc, out);
+    return;
+  }
   hipLaunchKernelGGL(k_pk_cross, dim3((unsigned)nchunk, (unsigned)nbins), dim3(kPT), 0, s, sd, sp, ng,
                      padded_cols(ng), kf, kmax, vol_fac, edges, nbins, axis, partial, nchunk);
   hipLaunchKernelGGL(k_pk_cross_reduce, dim3((unsigned)((nbins + 63) / 64)), dim3(64), 0, s, partial, nbins,
                      nchunk, out);
 }
 
+// Sums of |k|, P and the mode count per bin (out: 3 per bin).
 void launch_pk_bin(const float2* spec, int ng, double box, const double* edges, int nbins,
-                   double* partial, int nchunk, hipStream_t s, int deconvolve) {
+                   double* partial, int nchunk, double* out, hipStream_t s, int deconvolve) {
   const double pi = 3.14159265358979323846;
   const double kf = 2.0 * pi / box;
   const double kmax = pi * ng / box;
   const double v = box * box * box;
   const double n3 = (double)ng * ng * ng;
   const double vol_fac = (v / n3) * (v / n3) / v;  // |(V/Ng^3) X|^2 / V
+  int nc = 0;
+  if (pk_rows_plan(ng, nbins, 3, kPkPartialDoubles, &nc)) {
+    hipLaunchKernelGGL(k_pk_rows<false>, dim3((unsigned)nc), dim3(64 * kRowWaves), pk_rows_lds(ng, nbins, 2), s, spec,
+                       nullptr, ng, padded_cols(ng), kf, kmax, vol_fac, edges, nbins, 0, partial, nc, deconvolve);
+    hipLaunchKernelGGL(k_pk_rows_reduce<3>, dim3((unsigned)nbins), dim3(256), 0, s, partial, nc, out);
+    return;
+  }
   hipLaunchKernelGGL(k_pk_bin, dim3((unsigned)nchunk, (unsigned)nbins), dim3(kPT), 0, s, spec, ng,
                      padded_cols(ng), kf, kmax, vol_fac, edges, nbins, partial, nchunk, deconvolve);
+  hipLaunchKernelGGL(k_pk_reduce, dim3((unsigned)((nbins + 63) / 64)), dim3(64), 0, s, partial, nbins,
+                     nchunk, out);
 }
 
 // Smoothing + aliasing correction of Jing (2005) (Sec. 3.3): per bin b, the
@@ -310,11 +598,6 @@ void launch_pk_alias(int ng, double box, const double* edges, int nbins, const d
   hipLaunchKernelGGL(k_pk_alias, dim3((unsigned)nchunk, (unsigned)nbins), dim3(kPT), 0, s, ng, kf, kmax, edges,
                      nbins, slope, partial, nchunk);
   hipLaunchKernelGGL(k_pk_alias_reduce, dim3((unsigned)((nbins + 63) / 64)), dim3(64), 0, s, partial, nbins,
-                     nchunk, out);
-}
-
-void launch_pk_reduce(const double* partial, int nbins, int nchunk, double* out, hipStream_t s) {
-  hipLaunchKernelGGL(k_pk_reduce, dim3((unsigned)((nbins + 63) / 64)), dim3(64), 0, s, partial, nbins,
                      nchunk, out);
 }
 
