@@ -232,7 +232,8 @@ int cola_pk_velocity(cola_ctx* ctx, int32_t axis, const double* k_edges, int32_t
  * dx -= nmesh rint(dx/nmesh), r2 = (dx0^2 + dx1^2) + dx2^2 <= float(b^2),
  * one rounding per operation.  dev_work: cola_fof_workspace_bytes bytes of
  * 256-byte aligned device memory, owned by the caller.  Overwrites the tile
- * sort's scratch (rebuilt by every deposit); synchronises the stream.
+ * sort's scratch and the force meshes (rebuilt by every call that uses them);
+ * synchronises the stream.
  * Errors: COLA_EINVAL (NULL pointers, b_frac out of range, misaligned
  * work), COLA_ENOMEM (work too small), COLA_ESTATE (no particle state, or a
  * union that exceeded its retry bound). */

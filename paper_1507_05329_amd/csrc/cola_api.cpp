@@ -822,10 +822,9 @@ int cola_fof(cola_ctx* c, double b_frac, int32_t* labels, void* work, size_t wor
   if (((uintptr_t)work & 255) != 0) return fail(c, COLA_EINVAL, "dev_work must be 256-byte aligned");
   if (work_bytes < fof_part(c->np3, 3)) return fail(c, COLA_ENOMEM, "dev_work smaller than cola_fof_workspace_bytes");
   char* w = static_cast<char*>(work);
-  launch_fill_u32(c->flag, 1, 0u, c->stream);
   launch_fof(c->disp, c->p.np, c->p.nmesh, b_frac, reinterpret_cast<uint32_t*>(labels),
              reinterpret_cast<uint32_t*>(w + fof_part(c->np3, 0)), reinterpret_cast<uint32_t*>(w + fof_part(c->np3, 1)),
-             reinterpret_cast<uint32_t*>(w + fof_part(c->np3, 2)), c->pkey, c->prank, c->perm, c->flag, c->stream);
+             reinterpret_cast<uint32_t*>(w + fof_part(c->np3, 2)), c->pkey, c->prank, c->perm, c->meshbase, c->flag, c->stream);
   LAUNCH_CHECK(c, "cola_fof");
   uint32_t h = 0;
   HIP_TRY(c, hipMemcpyAsync(&h, c->flag, sizeof(uint32_t), hipMemcpyDeviceToHost, c->stream));
@@ -866,7 +865,7 @@ int cola_fof_halos(cola_ctx* c, const int32_t* labels, const float* vel, int32_t
   char* w = static_cast<char*>(work);
   auto u32 = [&](int i) { return reinterpret_cast<uint32_t*>(w + halo_part(c->np3, min_members, i)); };
   launch_fill_u32(c->flag, 1, 0u, c->stream);
-  launch_halo_count(labels, c->np3, min_members, u32(0), u32(1), u32(2), u32(3), c->flag, c->stream);
+  launch_halo_count(labels, c->p.np, min_members, u32(0), u32(1), u32(2), u32(3), c->flag, c->stream);
   LAUNCH_CHECK(c, "cola_fof_halos");
   uint32_t h[2] = {0, 0};
   HIP_TRY(c, hipMemcpyAsync(&h[0], c->flag, sizeof(uint32_t), hipMemcpyDeviceToHost, c->stream));

@@ -77,10 +77,8 @@ void launch_bin_count(const float* disp, int np, int nm, float dscale, uint32_t*
                       uint32_t* pkey, uint32_t* prank, hipStream_t s, int nmock = 1, long mstride = 0);
 void launch_exclusive_scan(const uint32_t* in, uint32_t* out, long n,
                            uint32_t* scratch, hipStream_t s, int nmock = 1, long mstride = 0);
-void launch_scatter(const uint32_t* pkey, const uint32_t* prank, const uint32_t* off,
-                    long np3, uint32_t* perm, hipStream_t s, int nmock = 1, long mstride = 0);
-// The same scatter for the tile sort of np^3 lattice particles, walking them
-// as the bucket count does (np a multiple of 16).
+// Scatter of the tile sort of np^3 lattice particles, walking them as the
+// bucket count does (np a multiple of 16).
 void launch_scatter_walk(const uint32_t* pkey, const uint32_t* prank, const uint32_t* off, int np,
                          uint32_t* perm, hipStream_t s, int nmock = 1, long mstride = 0);
 // Deterministic CIC gather (k_deposit.hip).
@@ -209,15 +207,16 @@ void launch_pk_cross(const float2* sd, const float2* sp, int ng, double box, con
                      int axis, double* partial, int nchunk, double* out, hipStream_t s);
 // Friends-of-friends labels (k_fof.hip): labels[i] = smallest id of i's group.
 // count and start hold np^3 + 1 entries, scan_scratch (np^3 + 1) / 4096 + 2;
-// key, rank, sorted np^3 each; flag is set if a union exceeded its retry bound.
+// key, rank, par np^3 each, pos 16 np^3 bytes (16-byte aligned); flag (two words,
+// cleared here): the first is set if a union exceeded its retry bound.
 void launch_fof(const float* disp, int np, int nm, double b_frac, uint32_t* labels, uint32_t* count,
-                uint32_t* start, uint32_t* scan_scratch, uint32_t* key, uint32_t* rank, uint32_t* sorted,
+                uint32_t* start, uint32_t* scan_scratch, uint32_t* key, uint32_t* rank, uint32_t* par, void* pos,
                 uint32_t* flag, hipStream_t s);
 // Halo catalogue of FoF labels (k_fof.hip): count per label, flags of groups with
 // >= minm members, their exclusive scan (hidx[np3] = number of halos); then roots,
 // counts, centres and mean velocities (SoA with the given stride) from 64-bit
 // fixed-point sums (acc: 6 per halo).  bad is set for a label outside [0, np3).
-void launch_halo_count(const int32_t* lab, long np3, int32_t minm, uint32_t* count, uint32_t* flg, uint32_t* hidx,
+void launch_halo_count(const int32_t* lab, int np, int32_t minm, uint32_t* count, uint32_t* flg, uint32_t* hidx,
                        uint32_t* scan_scratch, uint32_t* bad, hipStream_t s);
 void launch_halo_fill(const float* disp, const float* vel, const int32_t* lab, const uint32_t* count,
                       const uint32_t* flg, const uint32_t* hidx, int np, int nm, int nh, int stride,

@@ -168,25 +168,6 @@ void launch_exclusive_scan(const uint32_t* in, uint32_t* out, long n, uint32_t* 
                      mstride);
 }
 
-__global__ __launch_bounds__(256) void k_scatter(const uint32_t* __restrict__ pkey,
-                                                 const uint32_t* __restrict__ prank,
-                                                 const uint32_t* __restrict__ off, long np3,
-                                                 uint32_t* __restrict__ perm, long mstride) {
-  pkey = mock_ptr(pkey, mstride);
-  prank = mock_ptr(prank, mstride);
-  off = mock_ptr(off, mstride);
-  perm = mock_ptr(perm, mstride);
-  const long i = blockIdx.x * (long)blockDim.x + threadIdx.x;
-  if (i >= np3) return;
-  perm[off[pkey[i]] + prank[i]] = (uint32_t)i;
-}
-
-void launch_scatter(const uint32_t* pkey, const uint32_t* prank, const uint32_t* off, long np3,
-                    uint32_t* perm, hipStream_t s, int nmock, long mstride) {
-  hipLaunchKernelGGL(k_scatter, dim3((unsigned)((np3 + 255) / 256), 1, (unsigned)nmock), dim3(256), 0, s,
-                     pkey, prank, off, np3, perm, mstride);
-}
-
 // The tile sort's scatter, in the bucket count's particle-to-workgroup walk:
 // the count reserved one contiguous run per (workgroup, bucket), so each
 // workgroup's writes fill a few whole runs instead of single ids scattered

@@ -53,6 +53,34 @@ def test_fof_labels_bit_exact(np_side, nm, box, b_frac):
         assert (sizes >= 32).sum() > 0
 
 
+@pytest.mark.parametrize("np_side,nm,b_frac,boxes,clump", [
+    (16, 32, 0.2, 1.0, 0.0), (16, 48, 0.37, 3.0, 0.3), (16, 32, 0.49, 0.0, 0.9), (16, 32, 0.3, 400.0, 0.5)])
+def test_fof_scattered_positions_bit_exact(np_side, nm, b_frac, boxes, clump):
+    """Displacements that leave nothing of the lattice: positions all over
+    ``boxes`` periods (400: beyond the coordinates whose rounding the search's
+    face test allows for, so it visits every neighbour cell), a share of them
+    in one clump across the corner of the box, against all pairs."""
+    from paper_1507_05329_amd.sim import ColaSim
+    say(f"[gpu] fof of scattered positions, {np_side}^3/{nm}^3 b = {b_frac}, {boxes} periods")
+    rng = np.random.default_rng(int(100 * b_frac))
+    n = np_side ** 3
+    d = rng.uniform(-0.5, 0.5, (3, n)) * nm * max(boxes, 1.0)
+    inside = rng.random(n) < clump
+    d[:, inside] = rng.normal(0.0, 0.08 * nm, (3, int(inside.sum()))) - fof.lattice_fp32(np_side, nm)[:, inside]
+    d = d.astype(np.float32)
+    sim = ColaSim(np_side, nm, 100.0)
+    try:
+        t = torch.from_numpy(d).cuda()
+        sim.set_state(t, t, t, t, 0.5, 0.5)
+        lab = [sim.fof(b_frac).cpu().numpy() for _ in range(3)]
+    finally:
+        sim.close()
+    ref = fof.fof_labels_brute(d, np_side, nm, b_frac)
+    assert len(np.unique(ref)) < n
+    for a in lab:
+        assert np.array_equal(a, ref)
+
+
 def test_fof_initial_lattice_is_all_singletons():
     # at a = 0.02 neighbours are about one separation apart, far beyond b = 0.2 of it
     from paper_1507_05329_amd.sim import ColaSim
