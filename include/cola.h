@@ -136,7 +136,7 @@ int cola_density(cola_ctx* ctx, float* dev_out);
 /* For callers that cannot allocate device memory (code under HIP graph
  * capture, tight serving loops, harnesses that forbid hipMalloc): the
  * density contrast of cola_density_of, computed without a context.  The
- * tile sort's buffers live in a static device array of 3.4 MB that each
+ * tile sort's buffers live in a static device array of 4.5 MB that each
  * device holds until the process ends; the call makes no allocation
  * (no hipMalloc, hipFree or host allocator) and enqueues the tile sort and
  * deposit kernels on hip_stream (a hipStream_t of the current device;

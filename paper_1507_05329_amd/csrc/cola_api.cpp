@@ -90,8 +90,8 @@ Layout layout(const cola_params* p) {
   L.vres = take(3 * np3 * sizeof(float));
   L.psi1 = take(3 * np3 * sizeof(float));
   L.psi2 = take(3 * np3 * sizeof(float));
-  L.pkey = take(np3 * sizeof(uint32_t));
-  L.prank = take(np3 * sizeof(uint32_t));
+  L.pkey = take(np3 * sizeof(uint32_t));   // pkey and prank are adjacent (np3 is a multiple of 4096):
+  L.prank = take(np3 * sizeof(uint32_t));  // the tile sort's records take both
   L.perm = take(np3 * sizeof(uint32_t));
   L.counts = take((L.nbucket + 1) * sizeof(uint32_t));
   L.offsets = take((L.nbucket + 1) * sizeof(uint32_t));
@@ -161,26 +161,30 @@ struct StageTimer {
 
 float2* ic_buf(cola_ctx* c, int i) { return c->meshbase + (size_t)i * mesh_complex_count(c->p.np); }
 
-// Tile sort of the current positions on an ng^3 grid.  Batched form: nmock
+// Tile sort of the positions disp on an ng^3 grid.  Batched form: nmock
 // contexts with identical layouts, mock b's workspace at byte offset b * mstride.
-void tile_sort(cola_ctx* c, int ng, const float* disp, int nmock = 1, long mstride = 0) {
+// rec: what the mass deposit reads, in the key, rank and adjoint scratch arrays
+// (8 + 8 bytes a particle); ids: the particle ids (the weighted deposit's).
+void tile_sort(cola_ctx* c, int ng, const float* disp, bool rec, bool ids, int nmock = 1, long mstride = 0) {
   StageTimer t(c, COLA_STAGE_SORT);
   const float dscale = (float)((double)ng / (double)c->p.nmesh);
-  const long nt = ng / 16;
-  const long nb = 8 * nt * nt * nt;
-  launch_fill_u32(c->counts, nb + 1, 0u, c->stream, nmock, mstride);
-  launch_bin_count(disp, c->p.np, ng, dscale, c->counts, c->pkey, c->prank, c->stream, nmock, mstride);
-  launch_exclusive_scan(c->counts, c->offsets, nb, c->scan_scratch, c->stream, nmock, mstride);
-  launch_scatter_walk(c->pkey, c->prank, c->offsets, c->p.np, c->perm, c->stream, nmock, mstride);
+  TileSort ts;
+  ts.cursor = c->counts;
+  ts.offsets = c->offsets;
+  ts.scan = c->scan_scratch;
+  ts.fxy = rec ? reinterpret_cast<float2*>(c->pkey) : nullptr;
+  ts.fzc = rec ? reinterpret_cast<float2*>(c->fbar) : nullptr;
+  ts.perm = ids ? c->perm : nullptr;
+  launch_tile_sort(disp, c->p.np, ng, dscale, ts, c->stream, nmock, mstride);
 }
 
+// ids: leave the sorted ids too (for a weighted deposit of the same positions).
 void deposit(cola_ctx* c, int ng, float* out, long row_stride, int contrast, const float* disp,
-             int nmock = 1, long mstride = 0) {
-  const float dscale = (float)((double)ng / (double)c->p.nmesh);
-  tile_sort(c, ng, disp, nmock, mstride);
+             int nmock = 1, long mstride = 0, bool ids = false) {
+  tile_sort(c, ng, disp, true, ids, nmock, mstride);
   StageTimer t(c, COLA_STAGE_DEPOSIT);
-  launch_deposit(disp, c->perm, c->offsets, c->p.np, ng, dscale, out, row_stride, contrast,
-                 c->stream, nmock, mstride);
+  launch_deposit(reinterpret_cast<const float2*>(c->pkey), reinterpret_cast<const float2*>(c->fbar), c->offsets,
+                 c->p.np, ng, out, row_stride, contrast, c->stream, nmock, mstride);
 }
 
 // Green's function scale: g_d = IDFT[i n_d gscale / |n|^2 DFT(delta)] in mesh
@@ -241,9 +245,9 @@ void fft_forces(cola_ctx* c, int nmock = 1, long mstride = 0) {
   }
 }
 
-void force_meshes(cola_ctx* c, const float* disp, int nmock = 1, long mstride = 0) {
+void force_meshes(cola_ctx* c, const float* disp, int nmock = 1, long mstride = 0, bool ids = false) {
   const int nm = c->p.nmesh;
-  deposit(c, nm, reinterpret_cast<float*>(c->mesh[0]), 2 * pm_rowc(nm), 1, disp, nmock, mstride);
+  deposit(c, nm, reinterpret_cast<float*>(c->mesh[0]), 2 * pm_rowc(nm), 1, disp, nmock, mstride, ids);
   fft_forces(c, nmock, mstride);
 }
 
@@ -775,7 +779,7 @@ int cola_pk_velocity(cola_ctx* c, int32_t axis, const double* edges, int32_t nbi
   // Mpc/h over nbar (momentum)
   launch_los_weights(g, force_row_stride(nm), c->disp, c->vres, c->psi1, c->psi2, c->p.np, nm, k, axis,
                      (float)(1.0 / nbar), (float)(c->p.box / nm / (a * adot) / nbar), c->fbar, c->stream);
-  tile_sort(c, nm, c->disp);
+  tile_sort(c, nm, c->disp, false, true);
   launch_deposit3_weighted(c->disp, c->perm, c->offsets, c->p.np, nm, c->fbar,
                            reinterpret_cast<float*>(c->mesh[0]), rs, 2 * c->mesh_stride, c->stream);
   fft3d_forward(c->mesh[0], nm, c->tw, c->stream);
@@ -948,11 +952,11 @@ int step_adjoint(cola_ctx* c, double a0, double a1, double a_v0, const float* di
   if (kept) {
     // the forward step's force field; sort the checkpointed positions for
     // the transposed readout below
-    tile_sort(c, nm, disp0);
+    tile_sort(c, nm, disp0, false, true);
     g = reinterpret_cast<const float*>(kept);
   } else {
     // forward force field at the checkpointed positions (also sorts them)
-    force_meshes(c, disp0);
+    force_meshes(c, disp0, 1, 0, true);
     g = force_field(c);
   }
   float* gbar = reinterpret_cast<float*>(c->mesh[0]);

@@ -70,21 +70,29 @@ double interp_pk(double k, const double* kt, const double* pt, int nk);
 
 // ---------------------------------------------------------------------------
 // Kernel launchers (all asynchronous on `s`).
-// Tile sort of particles by the 8^3 tile of their home cell (k_sort.hip).
+// Tile sort of particles by the 16^3 tile of their home cell (k_sort.hip).
 // Batched launches: nmock mocks, arrays of mock b at byte offset b * mstride.
 void launch_fill_u32(uint32_t* p, long n, uint32_t v, hipStream_t s, int nmock = 1, long mstride = 0);
-void launch_bin_count(const float* disp, int np, int nm, float dscale, uint32_t* counts,
-                      uint32_t* pkey, uint32_t* prank, hipStream_t s, int nmock = 1, long mstride = 0);
-void launch_exclusive_scan(const uint32_t* in, uint32_t* out, long n,
-                           uint32_t* scratch, hipStream_t s, int nmock = 1, long mstride = 0);
-// Scatter of the tile sort of np^3 lattice particles, walking them as the
-// bucket count does (np a multiple of 16).
-void launch_scatter_walk(const uint32_t* pkey, const uint32_t* prank, const uint32_t* off, int np,
-                         uint32_t* perm, hipStream_t s, int nmock = 1, long mstride = 0);
+// Exclusive scan of n entries into out[0 .. n] (out[n] = total), and into in
+// itself where both is not 0.  in, out: 16-byte aligned; scratch: n / 4096 + 2.
+void launch_exclusive_scan(uint32_t* in, uint32_t* out, long n, uint32_t* scratch, int both,
+                           hipStream_t s, int nmock = 1, long mstride = 0);
+// Tile sort of np^3 lattice particles (np a multiple of 16) on an nm^3 mesh.
+struct TileSort {
+  uint32_t* cursor;   // 8 (nm / 16)^3 + 1: counts, then starts, then ends of the buckets
+  uint32_t* offsets;  // 8 (nm / 16)^3 + 1: starts of the buckets
+  uint32_t* scan;     // scan scratch
+  // What lies at a particle's place, either part may be null: its fractions and
+  // cell within the tile (fxy = f_x, f_y; fzc = f_z, cell x 256 + y 16 + z), its id.
+  float2* fxy;
+  float2* fzc;
+  uint32_t* perm;
+};
+void launch_tile_sort(const float* disp, int np, int nm, float dscale, const TileSort& ts, hipStream_t s,
+                      int nmock = 1, long mstride = 0);
 // Deterministic CIC gather (k_deposit.hip).
-void launch_deposit(const float* disp, const uint32_t* perm, const uint32_t* off,
-                    int np, int nm, float dscale, float* out, long row_stride, int contrast,
-                    hipStream_t s, int nmock = 1, long mstride = 0);
+void launch_deposit(const float2* fxy, const float2* fzc, const uint32_t* off, int np, int nm, float* out,
+                    long row_stride, int contrast, hipStream_t s, int nmock = 1, long mstride = 0);
 // Three weighted deposits at once (readout transpose): out[q] += sum_p wt[q][p] w_s(p).
 void launch_deposit3_weighted(const float* disp, const uint32_t* perm, const uint32_t* off, int np,
                               int nm, const float* wt, float* out, long row_stride,

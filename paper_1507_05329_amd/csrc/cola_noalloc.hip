@@ -1,7 +1,7 @@
 // cola_density_noalloc: the deterministic CIC density of a displacement field
 // (the deposit of cola_density_of) for callers that cannot allocate device
-// memory.  The tile sort's buffers (bucket keys, ranks, permutation, bucket
-// counts and offsets, scan scratch) live in one file-scope device array of
+// memory.  The tile sort's buffers (records, bucket counts and offsets, scan
+// scratch) live in one file-scope device array of
 // fixed size; each device holds its own copy until the process ends.
 #include <atomic>
 
@@ -16,7 +16,7 @@ constexpr long kAlignWords = 64;  // 256 bytes
 constexpr long align_words(long n) { return (n + kAlignWords - 1) / kAlignWords * kAlignWords; }
 constexpr long buckets_of(int nm) { return 8L * (nm / 16) * (nm / 16) * (nm / 16); }
 constexpr long scratch_words(long np3, int nm) {
-  return 3 * align_words(np3) + 2 * align_words(buckets_of(nm) + 1) + align_words((buckets_of(nm) + 1) / 4096 + 2);
+  return 4 * align_words(np3) + 2 * align_words(buckets_of(nm) + 1) + align_words((buckets_of(nm) + 1) / 4096 + 2);
 }
 constexpr long kScratchWords = scratch_words(kMaxParticles, kMaxMesh);
 
@@ -57,19 +57,17 @@ extern "C" int cola_density_noalloc(const float* disp, int32_t np, int32_t nmesh
   const int r = scratch_address(&base);
   if (r != COLA_OK) return r;
   const long nb = buckets_of(nmesh);
-  uint32_t* pkey = base;
-  uint32_t* prank = pkey + align_words(np3);
-  uint32_t* perm = prank + align_words(np3);
-  uint32_t* counts = perm + align_words(np3);
-  uint32_t* offsets = counts + align_words(nb + 1);
-  uint32_t* scan = offsets + align_words(nb + 1);
+  cola::TileSort ts;
+  ts.fxy = reinterpret_cast<float2*>(base);
+  ts.fzc = reinterpret_cast<float2*>(base + 2 * align_words(np3));
+  ts.perm = nullptr;
+  ts.cursor = base + 4 * align_words(np3);
+  ts.offsets = ts.cursor + align_words(nb + 1);
+  ts.scan = ts.offsets + align_words(nb + 1);
   hipStream_t s = static_cast<hipStream_t>(stream);
-  // counts start at zero: cleared by a kernel on every call (the array keeps
+  // every buffer is written before it is read on every call (the array keeps
   // the previous call's contents)
-  cola::launch_fill_u32(counts, nb + 1, 0u, s);
-  cola::launch_bin_count(disp, np, nmesh, 1.0f, counts, pkey, prank, s);
-  cola::launch_exclusive_scan(counts, offsets, nb, scan, s);
-  cola::launch_scatter_walk(pkey, prank, offsets, np, perm, s);
-  cola::launch_deposit(disp, perm, offsets, np, nmesh, 1.0f, out, nmesh, 1, s);
+  cola::launch_tile_sort(disp, np, nmesh, 1.0f, ts, s);
+  cola::launch_deposit(ts.fxy, ts.fzc, ts.offsets, np, nmesh, out, nmesh, 1, s);
   return hipGetLastError() == hipSuccess ? COLA_OK : COLA_EHIP;
 }

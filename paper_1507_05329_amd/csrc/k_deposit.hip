@@ -12,6 +12,8 @@
 // the integer sum is exact, so the node mass float32(sum) 2^-32 does not
 // depend on the order of the particles, the buckets or the workgroups.  The
 // particles are streamed, never held, so a region of any size takes one pass.
+// What is read are the tile sort's records (fractions and cell in the tile, 16
+// bytes in bucket order), not ids and through them displacements.
 //
 // Weighted deposits (k_deposit, NC = 3: the transpose of the
 // three-component readout; weights of either sign and any size): particles
@@ -515,106 +517,198 @@ __global__ __launch_bounds__(kDT) void k_deposit(const float* __restrict__ disp,
   }
 }
 
-// Fixed-point mass deposit: node masses in units of 2^-32 particle masses.
+// Mass deposit.  Node masses in units of 2^-32 particle masses, on 17^3 nodes:
+// the layer past each upper face takes what belongs to the next tile (that
+// tile adds the same particles itself), so the tile's own particles need no
+// test.  39.5 KB: four workgroups per compute unit.
+constexpr int kAcc = kTile + 1;
 struct MassShared {
-  unsigned long long acc[kTile * kTile * kTile];   // 32 KB
-  uint32_t seg_start[kMaxSeg], seg_len[kMaxSeg];
-  uint32_t seg_pre[kMaxSeg];
-  uint32_t seg_total;
-  uint32_t offs[8][9];
-  int nseg;
+  unsigned long long acc[kAcc * kAcc * kAcc + 1];   // whole 16 bytes
 };
 
-constexpr float kFixScale = 4294967296.0f;           // 2^32
-constexpr float kFixInv = 2.3283064365386963e-10f;   // 2^-32
-constexpr int kMassG = 4;                            // particles in flight per thread
+// The region's boundary: bucket ranges [c0, c1) of lower neighbour (tx, ty, tz)
+// - (dx, dy, dz), nb = 4 dx + 2 dy + dz: the face classes that contain nb.
+// One hexadecimal digit per segment, the first one lowest.
+constexpr int kBnd = 13;
+constexpr uint64_t kBndNb = 0x7655433221111ull, kBndC0 = 0x7675473627531ull, kBndC1 = 0x8886884848642ull;
+__device__ __forceinline__ int bnd(uint64_t table, int q) { return (int)(table >> (4 * q)) & 15; }
 
-template <int kDT>
-__global__ __launch_bounds__(kDT) void k_deposit_mass(const float* __restrict__ disp,
-                                                      const uint32_t* __restrict__ perm,
-                                                      const uint32_t* __restrict__ off, int np, int nm,
-                                                      float dscale, long np3, float* __restrict__ out,
-                                                      long row_stride, int contrast, float cinv,
-                                                      long mstride) {
-  __shared__ MassShared sh;
-  disp = mock_ptr(disp, mstride);
-  perm = mock_ptr(perm, mstride);
+// rint(w 2^32), ties to even, for a weight w in [0, 1] (0 for NaN): below 1 it
+// fits 32 bits.
+__device__ __forceinline__ unsigned long long fix32(float w) {
+  const bool one = w >= 1.0f;
+  const uint32_t q = (uint32_t)__builtin_rintf(__fmul_rn(w, 4294967296.0f));   // saturates, 0 for NaN
+  return one ? 1ull << 32 : (unsigned long long)q;
+}
+
+// Adds a particle's weights to the nodes of offsets k with (k & nb) == nb
+// (nb = 0: all 8) of the cell whose offset-0 node is base.
+__device__ __forceinline__ void add_mass(MassShared& sh, const float f[3], int base, int nb) {
+#pragma unroll
+  for (int k = 0; k < 8; ++k)
+    if ((k & nb) == nb)
+      atomicAdd(&sh.acc[base + ((k >> 2) & 1) * kAcc * kAcc + ((k >> 1) & 1) * kAcc + (k & 1)],
+                fix32(cic_weight(f, k)));
+}
+
+constexpr float kFixInv = 2.3283064365386963e-10f;   // 2^-32
+template <int T, int G>
+__global__ __launch_bounds__(T) void k_deposit_mass(const float2* __restrict__ fxy, const float2* __restrict__ fzc,
+                                                    const uint32_t* __restrict__ off, int nm,
+                                                    float* __restrict__ out, long row_stride, int contrast,
+                                                    float cinv, long mstride) {
+  __shared__ __align__(16) MassShared sh;
+  fxy = mock_ptr(fxy, mstride);
+  fzc = mock_ptr(fzc, mstride);
   off = mock_ptr(off, mstride);
   out = mock_ptr(out, mstride);
   const int nt = nm / kTile;
   const uint32_t t = xcd_remap(blockIdx.x, gridDim.x);
   const int tx = t / (nt * nt), ty = (t / nt) % nt, tz = t % nt;
-  const int t0[3] = {tx * kTile, ty * kTile, tz * kTile};
-  for (int i = threadIdx.x; i < kTile * kTile * kTile; i += kDT) sh.acc[i] = 0ull;
-  setup_segments(sh, off, tx, ty, tz, nt);
+  // the tile's own particles: one contiguous range, its first records requested at once
+  const uint32_t s0 = off[t * 8u], s1 = off[t * 8u + 8u];
+  float2 a[G], b[G];
+#pragma unroll
+  for (int g = 0; g < G; ++g) {
+    const uint32_t x = s0 + g * T + threadIdx.x;
+    if (x < s1) {
+      a[g] = fxy[x];
+      b[g] = fzc[x];
+    }
+  }
+  // the boundary segments in lanes 0 .. 12 of every wave (first entry minus
+  // the entries before it, entries before it; lane 13: the total), so that a
+  // thread's first boundary record is requested before any barrier too
+  const int lane = threadIdx.x & 63;
+  uint32_t st = 0, len = 0;
+  if (lane < kBnd) {
+    const int nb = bnd(kBndNb, lane);
+    int ux = tx - (nb >> 2), uy = ty - ((nb >> 1) & 1), uz = tz - (nb & 1);
+    if (ux < 0) ux += nt;
+    if (uy < 0) uy += nt;
+    if (uz < 0) uz += nt;
+    const uint32_t* o = off + (((uint32_t)ux * nt + uy) * nt + uz) * 8u;
+    st = o[bnd(kBndC0, lane)];
+    len = o[bnd(kBndC1, lane)] - st;
+  }
+  uint32_t pre = len;
+#pragma unroll
+  for (int o = 1; o < 16; o <<= 1) {
+    const uint32_t v = __shfl_up(pre, o, 64);
+    if (lane >= o) pre += v;
+  }
+  pre -= len;
+  const uint32_t total = __shfl(pre, kBnd, 64);
+  int nb = 0;
+  auto bnd_place = [&](uint32_t x) -> uint32_t {   // record of boundary entry x; nb: its neighbour
+    int q = 0;                                     // last segment with pre <= x
+#pragma unroll
+    for (int step = 8; step > 0; step >>= 1) {
+      const uint32_t p = __shfl(pre, (q + step) & 15, 64);
+      if (q + step < kBnd && p <= x) q += step;
+    }
+    nb = bnd(kBndNb, q);
+    return __shfl(st - pre, q, 64) + x;
+  };
+  float2 ba = make_float2(0.f, 0.f), bb = ba;
+  if (total > 0) {
+    const uint32_t p = bnd_place(min(threadIdx.x, total - 1));
+    if (threadIdx.x < total) {
+      ba = fxy[p];
+      bb = fzc[p];
+    }
+  }
+  for (int i = threadIdx.x; i < kAcc * kAcc * kAcc / 2 + 1; i += T)
+    reinterpret_cast<ulonglong2*>(sh.acc)[i] = make_ulonglong2(0ull, 0ull);
+  __syncthreads();
 
-  const uint32_t total = sh.seg_total;
-  const int nseg = sh.nseg;
-  for (uint32_t base = 0; base < total; base += kMassG * kDT) {
-    uint32_t ids[kMassG];
+  for (uint32_t x0 = s0; x0 < s1; x0 += G * T) {
+    if (x0 > s0) {
 #pragma unroll
-    for (int g = 0; g < kMassG; ++g) {
-      const uint32_t x = base + g * kDT + threadIdx.x;
-      ids[g] = 0xffffffffu;
-      if (x < total) {
-        int sg = 0;  // last segment with seg_pre <= x
-#pragma unroll
-        for (int step = kMaxSeg / 2; step > 0; step >>= 1)
-          if (sg + step < nseg && sh.seg_pre[sg + step] <= x) sg += step;
-        ids[g] = perm[sh.seg_start[sg] + (x - sh.seg_pre[sg])];
+      for (int g = 0; g < G; ++g) {
+        const uint32_t x = x0 + g * T + threadIdx.x;
+        if (x < s1) {
+          a[g] = fxy[x];
+          b[g] = fzc[x];
+        }
       }
     }
-    int c[kMassG][3];
-    float f[kMassG][3];
 #pragma unroll
-    for (int g = 0; g < kMassG; ++g)
-      if (ids[g] != 0xffffffffu) home_cell(disp, np3, ids[g], np, nm, dscale, c[g], f[g]);
-#pragma unroll
-    for (int g = 0; g < kMassG; ++g) {
-      if (ids[g] == 0xffffffffu) continue;
-      // region coordinates 0..16; the tile's nodes are region 1..16, and a
-      // cell at r feeds nodes r and r + 1, i.e. tile nodes r - 1 and r
-      const int rx = region_coord(c[g][0], t0[0], nm), ry = region_coord(c[g][1], t0[1], nm),
-                rz = region_coord(c[g][2], t0[2], nm);
-      if (rx >= kReg || ry >= kReg || rz >= kReg) continue;
-#pragma unroll
-      for (int k = 0; k < 8; ++k) {
-        const int nx = rx + ((k >> 2) & 1) - 1, ny = ry + ((k >> 1) & 1) - 1, nz = rz + (k & 1) - 1;
-        if (nx < 0 || nx >= kTile || ny < 0 || ny >= kTile || nz < 0 || nz >= kTile) continue;
-        const unsigned long long q = __float2ull_rn(__fmul_rn(cic_weight(f[g], k), kFixScale));
-        atomicAdd(&sh.acc[(nx * kTile + ny) * kTile + nz], q);
+    for (int g = 0; g < G; ++g) {
+      if (x0 + g * T + threadIdx.x < s1) {
+        const float f[3] = {a[g].x, a[g].y, b[g].x};
+        const uint32_t c = __float_as_uint(b[g].y);
+        add_mass(sh, f, (int)(((c >> 8) * kAcc + ((c >> 4) & 15)) * kAcc + (c & 15)), 0);
       }
+    }
+  }
+  for (uint32_t x0 = 0; x0 < total; x0 += T) {     // every lane of a wave takes part in the search
+    const uint32_t x = x0 + threadIdx.x;
+    if (x0 > 0) {
+      const uint32_t p = bnd_place(min(x, total - 1));
+      if (x < total) {
+        ba = fxy[p];
+        bb = fzc[p];
+      }
+    }
+    if (x < total) {
+      const float f[3] = {ba.x, ba.y, bb.x};
+      const uint32_t c = __float_as_uint(bb.y);
+      const int lx = nb & 4 ? -1 : (int)(c >> 8), ly = nb & 2 ? -1 : (int)((c >> 4) & 15),
+                lz = nb & 1 ? -1 : (int)(c & 15);
+      add_mass(sh, f, (lx * kAcc + ly) * kAcc + lz, nb);
     }
   }
   __syncthreads();
 
   // four consecutive z nodes per thread and store (rows of the padded
   // layout and tile origins are 16-byte aligned)
-  for (int qd = threadIdx.x; qd < kTile * kTile * kTile / 4; qd += kDT) {
-    const int nn = qd * 4;
-    const int nx = nn / (kTile * kTile), ny = (nn / kTile) % kTile, nz = nn % kTile;
-    const long o = ((long)(t0[0] + nx) * nm + (t0[1] + ny)) * row_stride + (t0[2] + nz);
+  for (int qd = threadIdx.x; qd < kTile * kTile * kTile / 4; qd += T) {
+    const int nx = qd >> 6, ny = (qd >> 2) & 15, nz = (qd & 3) * 4;
+    const long o = ((long)(tx * kTile + nx) * nm + (ty * kTile + ny)) * row_stride + (tz * kTile + nz);
+    unsigned long long q[4];
     float r[4];
 #pragma unroll
+    for (int j = 0; j < 4; ++j) q[j] = sh.acc[(nx * kAcc + ny) * kAcc + nz + j];
+    // float32(sum): sums below one particle mass (most nodes of a sparse mesh) by one conversion
+    if (__any((uint32_t)((q[0] | q[1] | q[2] | q[3]) >> 32))) {
+#pragma unroll
+      for (int j = 0; j < 4; ++j) r[j] = __ull2float_rn(q[j]);
+    } else {
+#pragma unroll
+      for (int j = 0; j < 4; ++j) r[j] = __uint2float_rn((uint32_t)q[j]);
+    }
+#pragma unroll
     for (int j = 0; j < 4; ++j) {
-      r[j] = __fmul_rn(__ull2float_rn(sh.acc[nn + j]), kFixInv);
+      r[j] = __fmul_rn(r[j], kFixInv);
       if (contrast) r[j] = __fsub_rn(__fmul_rn(r[j], cinv), 1.0f);
     }
     *reinterpret_cast<float4*>(out + o) = make_float4(r[0], r[1], r[2], r[3]);
   }
 }
 
-// One 256-thread workgroup per tile, 33 KB of LDS (four tiles per compute
-// unit).  The result does not depend on the shape.
-void launch_deposit(const float* disp, const uint32_t* perm, const uint32_t* off, int np, int nm,
-                    float dscale, float* out, long row_stride, int contrast, hipStream_t s,
-                    int nmock, long mstride) {
+// One workgroup per tile; the result does not depend on the shape.  What
+// bounds it is a workgroup's chain of requests (bucket starts, records, the
+// density's store) with four workgroups per compute unit; sort and deposit
+// together, before (ids, then displacements through them) and now: 256^3 / 768^3
+// 1.32 -> 0.97 ms, 512^3 / 1024^3 5.25 -> 3.76 ms, 128^3 / 256^3 0.110 -> 0.081 ms.
+// Two tiles along z per workgroup, for stores of whole 128-byte lines, took
+// 0.74 against 0.76 ms and 2.17 against 2.17 ms (35 against 32 us at 256): not kept.
+// 1024 threads where a tile holds more than 1024 particles on average: with 256
+// threads its records come in many rounds (64^3 / 64^3: 44 us with the ids).
+void launch_deposit(const float2* fxy, const float2* fzc, const uint32_t* off, int np, int nm, float* out,
+                    long row_stride, int contrast, hipStream_t s, int nmock, long mstride) {
   const long np3 = (long)np * np * np;
   const int nt = nm / kTile;
   const long ntiles = (long)nt * nt * nt;
   const float cinv = (float)((double)nm * nm * nm / (double)np3);
-  hipLaunchKernelGGL(k_deposit_mass<256>, dim3((unsigned)ntiles, 1, (unsigned)nmock), dim3(256), 0, s, disp,
-                     perm, off, np, nm, dscale, np3, out, row_stride, contrast, cinv, mstride);
+  const dim3 grid((unsigned)ntiles, 1, (unsigned)nmock);
+  if (np3 > 1024 * ntiles)
+    hipLaunchKernelGGL((k_deposit_mass<1024, 2>), grid, dim3(1024), 0, s, fxy, fzc, off, nm, out, row_stride, contrast,
+                       cinv, mstride);
+  else
+    hipLaunchKernelGGL((k_deposit_mass<256, 2>), grid, dim3(256), 0, s, fxy, fzc, off, nm, out, row_stride, contrast,
+                       cinv, mstride);
 }
 
 void launch_deposit3_weighted(const float* disp, const uint32_t* perm, const uint32_t* off, int np,

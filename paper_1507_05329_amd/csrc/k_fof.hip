@@ -295,7 +295,7 @@ void launch_fof(const float* disp, int np, int nm, double b_frac, uint32_t* labe
   launch_fill_u32(flag, 2, 0u, s);
   launch_fill_u32(count, np3 + 1, 0u, s);
   hipLaunchKernelGGL(k_fof_cell, dim3(blocks), dim3(256), 0, s, disp, np, nm, np3, s_inv, count, key, rank, far);
-  launch_exclusive_scan(count, start, np3, scan_scratch, s);
+  launch_exclusive_scan(count, start, np3, scan_scratch, 0, s);
   hipLaunchKernelGGL(k_fof_scatter, dim3(blocks), dim3(256), 0, s, disp, np, nm, np3, key, rank, start, p4);
   hipLaunchKernelGGL(k_fof_hook, dim3(blocks), dim3(256), 0, s, p4, np, nm, np3, s_inv, b2, (float)b_frac, start, par);
   hipLaunchKernelGGL(k_fof_flatten, dim3(blocks), dim3(256), 0, s, par, np3);
@@ -437,7 +437,7 @@ void launch_halo_count(const int32_t* lab, int np, int32_t minm, uint32_t* count
   launch_fill_u32(count, np3, 0u, s);
   hipLaunchKernelGGL(k_halo_count, dim3(blocks), dim3(256), 0, s, lab, np, np3, count, bad);
   hipLaunchKernelGGL(k_halo_flag, dim3(blocks), dim3(256), 0, s, count, np3, (uint32_t)minm, flg);
-  launch_exclusive_scan(flg, hidx, np3, scan_scratch, s);
+  launch_exclusive_scan(flg, hidx, np3, scan_scratch, 0, s);
 }
 
 void launch_halo_fill(const float* disp, const float* vel, const int32_t* lab, const uint32_t* count,

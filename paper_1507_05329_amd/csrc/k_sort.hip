@@ -1,6 +1,15 @@
 // Tile sort for the deterministic CIC deposit: bucket = (16^3 tile of the home
-// cell, face class).  Integer atomics only; the order inside a bucket is left
-// to the deposit, which orders particles by id itself.
+// cell, face class).  Integer atomics only; the order inside a bucket is
+// arbitrary (the mass deposit does not depend on it, the weighted one orders
+// particles by id itself).
+//
+// Two passes over the displacements: the first counts, the second (after the
+// scan) finds each particle's place again and writes what the deposit reads
+// there, so nothing per particle is kept between them.  A workgroup of either
+// pass takes 1024 particles, four per thread with all loads issued first, and
+// counts them by bucket in an LDS table, so that its chain of dependent
+// requests (positions, table, one global atomic per bucket) is paid once per
+// 1024 particles.
 #include "cola_device.h"
 #include "cola_internal.h"
 
@@ -20,80 +29,206 @@ void launch_fill_u32(uint32_t* p, long n, uint32_t v, hipStream_t s, int nmock, 
                      mstride);
 }
 
-__global__ __launch_bounds__(256) void k_bin_count(const float* __restrict__ disp, int np, int nm,
-                                                   float dscale, long np3, uint32_t* __restrict__ counts,
-                                                   uint32_t* __restrict__ pkey,
-                                                   uint32_t* __restrict__ prank, long mstride) {
-  disp = mock_ptr(disp, mstride);
-  counts = mock_ptr(counts, mstride);
-  pkey = mock_ptr(pkey, mstride);
-  prank = mock_ptr(prank, mstride);
-  // Sub-cube order: a workgroup's particles share few buckets. Every supported
-  // np is a multiple of 16, so np^3 is a multiple of 256 and each thread of
-  // the grid has a particle.
-  const long i = subcube_particle(xcd_remap(blockIdx.x, gridDim.x), threadIdx.x, np);
-  int c[3];
-  float f[3];
-  home_cell(disp, np3, (uint32_t)i, np, nm, dscale, c, f);
-  const uint32_t b = bucket_of(c, nm >> 4);
-  pkey[i] = b;
-  // Workgroup-aggregated count: an LDS table (open addressing, 512 slots for
-  // at most 256 keys) counts the workgroup's particles per bucket, then one
-  // global atomic per distinct bucket reserves their places.
-  constexpr uint32_t kEmpty = 0xffffffffu, kSlots = 512;
-  __shared__ uint32_t hkey[kSlots], hcnt[kSlots], hbase[kSlots];
-  for (uint32_t j = threadIdx.x; j < kSlots; j += 256) {
-    hkey[j] = kEmpty;
-    hcnt[j] = 0u;
+// LDS table of a workgroup's buckets: open addressing, at most 1024 keys.
+constexpr uint32_t kSlots = 2048, kEmpty = 0xffffffffu;
+constexpr int kPer = 4;                // particles per thread
+
+struct BinTable {
+  uint32_t key[kSlots], cnt[kSlots];
+};
+
+__device__ __forceinline__ void table_clear(BinTable& h) {
+  for (uint32_t j = threadIdx.x; j < kSlots / 4; j += 256) {
+    reinterpret_cast<uint4*>(h.key)[j] = make_uint4(kEmpty, kEmpty, kEmpty, kEmpty);
+    reinterpret_cast<uint4*>(h.cnt)[j] = make_uint4(0u, 0u, 0u, 0u);
   }
-  __syncthreads();
-  uint32_t h = (b * 2654435761u) >> 23;
-  for (;;) {
-    const uint32_t prev = atomicCAS(&hkey[h], kEmpty, b);
-    if (prev == kEmpty || prev == b) break;
-    h = (h + 1) & (kSlots - 1);
-  }
-  const uint32_t local = atomicAdd(&hcnt[h], 1u);
-  __syncthreads();
-  for (uint32_t j = threadIdx.x; j < kSlots; j += 256)
-    if (hkey[j] != kEmpty) hbase[j] = atomicAdd(&counts[hkey[j]], hcnt[j]);
-  __syncthreads();
-  prank[i] = hbase[h] + local;
 }
 
-void launch_bin_count(const float* disp, int np, int nm, float dscale, uint32_t* counts,
-                      uint32_t* pkey, uint32_t* prank, hipStream_t s, int nmock, long mstride) {
-  const long np3 = (long)np * np * np;
-  hipLaunchKernelGGL(k_bin_count, dim3((unsigned)((np3 + 255) / 256), 1, (unsigned)nmock), dim3(256), 0,
-                     s, disp, np, nm, dscale, np3, counts, pkey, prank, mstride);
+__device__ __forceinline__ uint32_t table_slot(BinTable& h, uint32_t b) {
+  uint32_t s = (b * 2654435761u) >> 21;
+  for (;;) {
+    const uint32_t prev = atomicCAS(&h.key[s], kEmpty, b);
+    if (prev == kEmpty || prev == b) return s;
+    s = (s + 1) & (kSlots - 1);
+  }
+}
+
+// Particle u (0 .. 3) of thread t in block b of np^3 / 1024: four sub-cubes of
+// subcube_particle stacked along i (8 x 4 x 32 ids, 16 x 4 x 16 when np is not
+// a multiple of 32): few buckets per workgroup.
+__device__ __forceinline__ long sort_particle(uint32_t b, int t, int u, int np) {
+  const int lk = (np & 31) == 0 ? 5 : 4;
+  const uint32_t layer = ((uint32_t)np >> lk) * ((uint32_t)np >> 2);   // sub-cubes per layer along i
+  const uint32_t bi = b / layer;
+  return subcube_particle((bi * kPer + u) * layer + (b - bi * layer), t, np);
+}
+
+__global__ __launch_bounds__(256) void k_tile_count(const float* __restrict__ disp, int np, int nm, float dscale,
+                                                    long np3, uint32_t* __restrict__ counts, long mstride) {
+  __shared__ __align__(16) BinTable h;
+  disp = mock_ptr(disp, mstride);
+  counts = mock_ptr(counts, mstride);
+  const uint32_t blk = xcd_remap(blockIdx.x, gridDim.x);
+  long id[kPer];
+  float d[kPer][3];
+#pragma unroll
+  for (int u = 0; u < kPer; ++u) {
+    id[u] = sort_particle(blk, threadIdx.x, u, np);
+#pragma unroll
+    for (int e = 0; e < 3; ++e) d[u][e] = disp[e * np3 + id[u]];
+  }
+  table_clear(h);
+  __syncthreads();
+#pragma unroll
+  for (int u = 0; u < kPer; ++u) {
+    int c[3];
+    float f[3];
+    home_cell_of(d[u], (uint32_t)id[u], np, nm, dscale, c, f);
+    atomicAdd(&h.cnt[table_slot(h, bucket_of(c, nm >> 4))], 1u);
+  }
+  __syncthreads();
+  for (uint32_t j = threadIdx.x; j < kSlots; j += 256)
+    if (h.key[j] != kEmpty) atomicAdd(&counts[h.key[j]], h.cnt[j]);
+}
+
+// cursor: the buckets' starts, advanced to their ends.  REC: fractions and
+// cell-in-tile of each particle (fxy, fzc) at its place; PERM: its id.
+template <bool REC, bool PERM>
+__global__ __launch_bounds__(256) void k_tile_fill(const float* __restrict__ disp, int np, int nm, float dscale,
+                                                   long np3, uint32_t* __restrict__ cursor, float2* __restrict__ fxy,
+                                                   float2* __restrict__ fzc, uint32_t* __restrict__ perm,
+                                                   long mstride) {
+  __shared__ __align__(16) BinTable h;
+  disp = mock_ptr(disp, mstride);
+  cursor = mock_ptr(cursor, mstride);
+  const uint32_t blk = xcd_remap(blockIdx.x, gridDim.x);
+  long id[kPer];
+  float d[kPer][3];
+#pragma unroll
+  for (int u = 0; u < kPer; ++u) {
+    id[u] = sort_particle(blk, threadIdx.x, u, np);
+#pragma unroll
+    for (int e = 0; e < 3; ++e) d[u][e] = disp[e * np3 + id[u]];
+  }
+  table_clear(h);
+  __syncthreads();
+  uint32_t slot[kPer], rank[kPer], cell[kPer];
+#pragma unroll
+  for (int u = 0; u < kPer; ++u) {
+    int c[3];
+    float f[3];
+    home_cell_of(d[u], (uint32_t)id[u], np, nm, dscale, c, f);
+    slot[u] = table_slot(h, bucket_of(c, nm >> 4));
+    rank[u] = atomicAdd(&h.cnt[slot[u]], 1u);
+    cell[u] = (uint32_t)(((c[0] & 15) << 8) | ((c[1] & 15) << 4) | (c[2] & 15));
+#pragma unroll
+    for (int e = 0; e < 3; ++e) d[u][e] = f[e];
+  }
+  __syncthreads();
+  for (uint32_t j = threadIdx.x; j < kSlots; j += 256)
+    if (h.key[j] != kEmpty) h.cnt[j] = atomicAdd(&cursor[h.key[j]], h.cnt[j]);
+  __syncthreads();
+  if constexpr (REC) {
+    fxy = mock_ptr(fxy, mstride);
+    fzc = mock_ptr(fzc, mstride);
+  }
+  if constexpr (PERM) perm = mock_ptr(perm, mstride);
+#pragma unroll
+  for (int u = 0; u < kPer; ++u) {
+    const uint32_t p = h.cnt[slot[u]] + rank[u];
+    if constexpr (REC) {
+      fxy[p] = make_float2(d[u][0], d[u][1]);
+      fzc[p] = make_float2(d[u][2], __uint_as_float(cell[u]));
+    }
+    if constexpr (PERM) perm[p] = (uint32_t)id[u];
+  }
 }
 
 // ---------------------------------------------------------------------------
-// Exclusive scan, three passes: block sums, scan of block sums, block scan.
+// Exclusive scan.  Up to kScanOne entries: one workgroup.  More: block sums,
+// scan of block sums, block scan.  in receives the scan as well (the fill's
+// cursor) where both is set.
 constexpr int kScanT = 256;
 constexpr int kScanPer = 16;
 constexpr long kScanChunk = (long)kScanT * kScanPer;
+constexpr int kScanOneT = 1024;
+constexpr long kScanOne = 65536;
 
+// Exclusive prefix of v over the workgroup (T threads) and the total.
+template <int T>
 __device__ __forceinline__ uint32_t block_exclusive_scan(uint32_t v, uint32_t* sh, uint32_t* total) {
-  // sh: kScanT entries.  Hillis-Steele in LDS (deterministic for integers anyway).
-  const int t = threadIdx.x;
-  sh[t] = v;
-  __syncthreads();
-  for (int off = 1; off < kScanT; off <<= 1) {
-    const uint32_t a = t >= off ? sh[t - off] : 0u;
-    __syncthreads();
-    sh[t] += a;
-    __syncthreads();
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  uint32_t incl = v;
+#pragma unroll
+  for (int off = 1; off < 64; off <<= 1) {
+    const uint32_t a = __shfl_up(incl, off, 64);
+    if (lane >= off) incl += a;
   }
-  const uint32_t incl = sh[t];
-  *total = sh[kScanT - 1];
+  __syncthreads();                     // sh may still be read from an earlier call
+  if (lane == 63) sh[wave] = incl;
   __syncthreads();
-  return incl - v;
+  uint32_t before = 0, all = 0;
+#pragma unroll
+  for (int w = 0; w < T / 64; ++w) {
+    const uint32_t s = sh[w];
+    before += w < wave ? s : 0u;
+    all += s;
+  }
+  *total = all;
+  return before + incl - v;
+}
+
+// kQ consecutive entries per thread and round (a multiple of 4).
+template <int kQ>
+__global__ __launch_bounds__(kScanOneT) void k_scan_one(uint32_t* __restrict__ in, uint32_t* __restrict__ out, long n,
+                                                        int both, long mstride) {
+  __shared__ uint32_t sh[kScanOneT / 64];
+  in = mock_ptr(in, mstride);
+  out = mock_ptr(out, mstride);
+  uint32_t carry = 0;
+  for (long base = 0; base < n; base += kScanOneT * kQ) {
+    const long i = base + (long)threadIdx.x * kQ;
+    uint4 v[kQ / 4];
+    uint32_t loc = 0;
+#pragma unroll
+    for (int j = 0; j < kQ / 4; ++j) {
+      const long p = i + 4 * j;
+      if (p + 4 <= n) {
+        v[j] = *reinterpret_cast<const uint4*>(in + p);
+      } else {
+        v[j] = make_uint4(p < n ? in[p] : 0u, p + 1 < n ? in[p + 1] : 0u, p + 2 < n ? in[p + 2] : 0u, 0u);
+      }
+    }
+#pragma unroll
+    for (int j = 0; j < kQ / 4; ++j) loc += (v[j].x + v[j].y) + (v[j].z + v[j].w);
+    uint32_t tot;
+    uint32_t ex = block_exclusive_scan<kScanOneT>(loc, sh, &tot) + carry;
+#pragma unroll
+    for (int j = 0; j < kQ / 4; ++j) {
+      const long p = i + 4 * j;
+      const uint32_t s1 = ex + v[j].x, s2 = s1 + v[j].y, s3 = s2 + v[j].z;
+      const uint4 o = make_uint4(ex, s1, s2, s3);
+      ex = s3 + v[j].w;
+      if (p + 4 <= n) {
+        *reinterpret_cast<uint4*>(out + p) = o;
+        if (both) *reinterpret_cast<uint4*>(in + p) = o;
+      } else {
+        const uint32_t q[3] = {o.x, o.y, o.z};
+        for (int u = 0; u < 3; ++u)
+          if (p + u < n) {
+            out[p + u] = q[u];
+            if (both) in[p + u] = q[u];
+          }
+      }
+    }
+    carry += tot;
+  }
+  if (threadIdx.x == 0) out[n] = carry;
 }
 
 __global__ __launch_bounds__(kScanT) void k_scan_reduce(const uint32_t* __restrict__ in, long n,
                                                         uint32_t* __restrict__ bsum, long mstride) {
-  __shared__ uint32_t sh[kScanT];
+  __shared__ uint32_t sh[kScanT / 64];
   in = mock_ptr(in, mstride);
   bsum = mock_ptr(bsum, mstride);
   const long base = blockIdx.x * kScanChunk;
@@ -103,14 +238,14 @@ __global__ __launch_bounds__(kScanT) void k_scan_reduce(const uint32_t* __restri
     if (i < n) acc += in[i];
   }
   uint32_t tot;
-  block_exclusive_scan(acc, sh, &tot);
+  block_exclusive_scan<kScanT>(acc, sh, &tot);
   if (threadIdx.x == 0) bsum[blockIdx.x] = tot;
 }
 
-// Scans nb <= kScanT*kScanPer*... block sums in place with one workgroup.
+// Scans the block sums in place with one workgroup.
 __global__ __launch_bounds__(kScanT) void k_scan_blocksums(uint32_t* __restrict__ bsum, long nb,
                                                            long mstride) {
-  __shared__ uint32_t sh[kScanT];
+  __shared__ uint32_t sh[kScanT / 64];
   bsum = mock_ptr(bsum, mstride);
   uint32_t carry = 0;
   for (long base = 0; base < nb; base += kScanT * (long)kScanPer) {
@@ -122,7 +257,7 @@ __global__ __launch_bounds__(kScanT) void k_scan_blocksums(uint32_t* __restrict_
       loc += v[j];
     }
     uint32_t tot;
-    uint32_t ex = block_exclusive_scan(loc, sh, &tot) + carry;
+    uint32_t ex = block_exclusive_scan<kScanT>(loc, sh, &tot) + carry;
     for (int j = 0; j < kScanPer; ++j) {
       const long i = base + (long)threadIdx.x * kScanPer + j;
       if (i < nb) bsum[i] = ex;
@@ -132,63 +267,89 @@ __global__ __launch_bounds__(kScanT) void k_scan_blocksums(uint32_t* __restrict_
   }
 }
 
-__global__ __launch_bounds__(kScanT) void k_scan_apply(const uint32_t* __restrict__ in, long n,
+// Four rounds of 1024 entries, four consecutive ones per thread (16-byte
+// accesses; the arrays are 16-byte aligned).
+__global__ __launch_bounds__(kScanT) void k_scan_apply(uint32_t* __restrict__ in, long n,
                                                        const uint32_t* __restrict__ bsum,
-                                                       uint32_t* __restrict__ out, long mstride) {
-  __shared__ uint32_t sh[kScanT];
+                                                       uint32_t* __restrict__ out, int both, long mstride) {
+  __shared__ uint32_t sh[kScanT / 64];
   in = mock_ptr(in, mstride);
   bsum = mock_ptr(bsum, mstride);
   out = mock_ptr(out, mstride);
-  const long base = blockIdx.x * kScanChunk + (long)threadIdx.x * kScanPer;
-  uint32_t v[kScanPer];
-  uint32_t loc = 0;
-  for (int j = 0; j < kScanPer; ++j) {
-    const long i = base + j;
-    v[j] = i < n ? in[i] : 0u;
-    loc += v[j];
+  constexpr int kR = kScanPer / 4;
+  const long base = blockIdx.x * kScanChunk + (long)threadIdx.x * 4;
+  uint4 v[kR];
+#pragma unroll
+  for (int r = 0; r < kR; ++r) {
+    const long i = base + r * 4L * kScanT;
+    if (i + 4 <= n) {
+      v[r] = *reinterpret_cast<const uint4*>(in + i);
+    } else {
+      v[r].x = i < n ? in[i] : 0u;
+      v[r].y = i + 1 < n ? in[i + 1] : 0u;
+      v[r].z = i + 2 < n ? in[i + 2] : 0u;
+      v[r].w = 0u;
+    }
   }
-  uint32_t tot;
-  uint32_t ex = block_exclusive_scan(loc, sh, &tot) + bsum[blockIdx.x];
-  for (int j = 0; j < kScanPer; ++j) {
-    const long i = base + j;
-    if (i < n) out[i] = ex;
-    ex += v[j];
+  uint32_t carry = bsum[blockIdx.x];
+#pragma unroll
+  for (int r = 0; r < kR; ++r) {
+    const long i = base + r * 4L * kScanT;
+    uint32_t tot;
+    const uint32_t s1 = v[r].x, s2 = s1 + v[r].y, s3 = s2 + v[r].z;
+    const uint32_t ex = block_exclusive_scan<kScanT>(s3 + v[r].w, sh, &tot) + carry;
+    const uint4 o = make_uint4(ex, ex + s1, ex + s2, ex + s3);
+    carry += tot;
+    if (i + 4 <= n) {
+      *reinterpret_cast<uint4*>(out + i) = o;
+      if (both) *reinterpret_cast<uint4*>(in + i) = o;
+    } else {
+      const uint32_t q[3] = {o.x, o.y, o.z};
+      for (int j = 0; j < 3; ++j)
+        if (i + j < n) {
+          out[i + j] = q[j];
+          if (both) in[i + j] = q[j];
+        }
+    }
+    // out[n] = total, written by the thread that holds element n-1
+    if (i < n && n <= i + 4) out[n] = ex + s3 + v[r].w;
   }
-  // out[n] = total, written by the thread that holds element n-1
-  if (base <= n - 1 && n - 1 < base + kScanPer) out[n] = ex;
 }
 
-void launch_exclusive_scan(const uint32_t* in, uint32_t* out, long n, uint32_t* scratch,
+void launch_exclusive_scan(uint32_t* in, uint32_t* out, long n, uint32_t* scratch, int both,
                            hipStream_t s, int nmock, long mstride) {
-  const long nb = (n + kScanChunk - 1) / kScanChunk;
   const unsigned z = (unsigned)nmock;
+  if (n <= kScanOne) {
+    if (n <= 4L * kScanOneT)
+      hipLaunchKernelGGL(k_scan_one<4>, dim3(1, 1, z), dim3(kScanOneT), 0, s, in, out, n, both, mstride);
+    else
+      hipLaunchKernelGGL(k_scan_one<32>, dim3(1, 1, z), dim3(kScanOneT), 0, s, in, out, n, both, mstride);
+    return;
+  }
+  const long nb = (n + kScanChunk - 1) / kScanChunk;
   hipLaunchKernelGGL(k_scan_reduce, dim3((unsigned)nb, 1, z), dim3(kScanT), 0, s, in, n, scratch, mstride);
   hipLaunchKernelGGL(k_scan_blocksums, dim3(1, 1, z), dim3(kScanT), 0, s, scratch, nb, mstride);
-  hipLaunchKernelGGL(k_scan_apply, dim3((unsigned)nb, 1, z), dim3(kScanT), 0, s, in, n, scratch, out,
+  hipLaunchKernelGGL(k_scan_apply, dim3((unsigned)nb, 1, z), dim3(kScanT), 0, s, in, n, scratch, out, both,
                      mstride);
 }
 
-// The tile sort's scatter, in the bucket count's particle-to-workgroup walk:
-// the count reserved one contiguous run per (workgroup, bucket), so each
-// workgroup's writes fill a few whole runs instead of single ids scattered
-// over many.  The result is the same in any walk (every id has its slot).
-__global__ __launch_bounds__(256) void k_scatter_walk(const uint32_t* __restrict__ pkey,
-                                                      const uint32_t* __restrict__ prank,
-                                                      const uint32_t* __restrict__ off, int np,
-                                                      uint32_t* __restrict__ perm, long mstride) {
-  pkey = mock_ptr(pkey, mstride);
-  prank = mock_ptr(prank, mstride);
-  off = mock_ptr(off, mstride);
-  perm = mock_ptr(perm, mstride);
-  const long i = subcube_particle(xcd_remap(blockIdx.x, gridDim.x), threadIdx.x, np);
-  perm[off[pkey[i]] + prank[i]] = (uint32_t)i;
-}
-
-void launch_scatter_walk(const uint32_t* pkey, const uint32_t* prank, const uint32_t* off, int np,
-                         uint32_t* perm, hipStream_t s, int nmock, long mstride) {
+void launch_tile_sort(const float* disp, int np, int nm, float dscale, const TileSort& ts, hipStream_t s, int nmock,
+                      long mstride) {
   const long np3 = (long)np * np * np;   // np is a multiple of 16: whole workgroups
-  hipLaunchKernelGGL(k_scatter_walk, dim3((unsigned)(np3 / 256), 1, (unsigned)nmock), dim3(256), 0, s,
-                     pkey, prank, off, np, perm, mstride);
+  const long nt = nm / 16, nb = 8 * nt * nt * nt;
+  const dim3 grid((unsigned)(np3 / (256 * kPer)), 1, (unsigned)nmock);
+  launch_fill_u32(ts.cursor, nb + 1, 0u, s, nmock, mstride);
+  hipLaunchKernelGGL(k_tile_count, grid, dim3(256), 0, s, disp, np, nm, dscale, np3, ts.cursor, mstride);
+  launch_exclusive_scan(ts.cursor, ts.offsets, nb, ts.scan, 1, s, nmock, mstride);
+  if (ts.fxy && ts.perm)
+    hipLaunchKernelGGL((k_tile_fill<true, true>), grid, dim3(256), 0, s, disp, np, nm, dscale, np3, ts.cursor, ts.fxy,
+                       ts.fzc, ts.perm, mstride);
+  else if (ts.fxy)
+    hipLaunchKernelGGL((k_tile_fill<true, false>), grid, dim3(256), 0, s, disp, np, nm, dscale, np3, ts.cursor, ts.fxy,
+                       ts.fzc, nullptr, mstride);
+  else
+    hipLaunchKernelGGL((k_tile_fill<false, true>), grid, dim3(256), 0, s, disp, np, nm, dscale, np3, ts.cursor, nullptr,
+                       nullptr, ts.perm, mstride);
 }
 
 }  // namespace cola
