@@ -311,13 +311,20 @@ int ic_from_mesh_noise(cola_ctx* c, const double* k, const double* pk, int nk) {
   const int np = c->p.np, nm = c->p.nmesh;
   const long rs = 2 * padded_cols(np);
   const double box = c->p.box;
-  // amplitude table sqrt(P(|k|) / dq^3) by integer |n|^2
-  std::vector<float> amp(c->amp_len);
+  // amplitude table sqrt(P(|k|) / dq^3) by integer |n|^2, from the table's
+  // copy in the P(k) partials (a longer table than they hold: on the host)
   const double kf = 2.0 * kPi / box, dq3 = std::pow(box / np, 3);
-  for (long n2 = 0; n2 < c->amp_len; ++n2)
-    amp[n2] = n2 == 0 ? 0.f : (float)std::sqrt(interp_pk(kf * std::sqrt((double)n2), k, pk, nk) / dq3);
-  HIP_TRY(c, hipMemcpyAsync(c->amp, amp.data(), amp.size() * sizeof(float), hipMemcpyHostToDevice,
-                            c->stream));
+  std::vector<float> amp;
+  if (2 * (long)nk <= kPkPartialDoubles) {
+    HIP_TRY(c, hipMemcpyAsync(c->pk_partial, k, nk * sizeof(double), hipMemcpyHostToDevice, c->stream));
+    HIP_TRY(c, hipMemcpyAsync(c->pk_partial + nk, pk, nk * sizeof(double), hipMemcpyHostToDevice, c->stream));
+    launch_amp_table(c->amp, c->amp_len, kf, dq3, c->pk_partial, c->pk_partial + nk, nk, c->stream);
+  } else {
+    amp.resize(c->amp_len);
+    for (long n2 = 0; n2 < c->amp_len; ++n2)
+      amp[n2] = n2 == 0 ? 0.f : (float)std::sqrt(interp_pk(kf * std::sqrt((double)n2), k, pk, nk) / dq3);
+    HIP_TRY(c, hipMemcpyAsync(c->amp, amp.data(), amp.size() * sizeof(float), hipMemcpyHostToDevice, c->stream));
+  }
   float2* A = ic_buf(c, 0);
   float2* B[3] = {ic_buf(c, 1), ic_buf(c, 2), ic_buf(c, 3)};
   // delta_L(k) = DFT[w] sqrt(P / dq^3), k = 0 and Nyquist-index modes zeroed
@@ -375,7 +382,7 @@ int ic_from_mesh_noise(cola_ctx* c, const double* k, const double* pk, int nk) {
                         (float)growth_D1(a0, c->p.omega_m), (float)D2_of(&c->p, a0),
                         c->stream);
   LAUNCH_CHECK(c, "init_2lpt");
-  HIP_TRY(c, hipStreamSynchronize(c->stream));  // the amplitude table's host copy is released here
+  HIP_TRY(c, hipStreamSynchronize(c->stream));  // the caller's table has been read
   c->a_x = c->a_v = a0;
   c->have_state = true;
   return COLA_OK;

@@ -190,6 +190,9 @@ void launch_readout_kick_drift(const float* g, long row_stride, float* disp, flo
                                int nmock = 1, long mstride = 0);
 // Initial conditions (k_ic.hip).
 void launch_philox_noise(uint64_t seed, int np, float* out, long row_stride, hipStream_t s);
+// Amplitudes by |n|^2 (k_ic.hip); kt, pt: device copies of the P(k) table.
+void launch_amp_table(float* amp, long n, double kf, double dq3, const double* kt, const double* pt, int nk,
+                      hipStream_t s);
 void launch_copy_to_mesh(const float* src, int n, float* mesh, long row_stride, hipStream_t s);
 // elem: floats between consecutive nodes of a row (3 for one component of the force field).
 void launch_copy_from_mesh(const float* mesh, int n, long row_stride, float* dst, float scale,
