@@ -309,7 +309,6 @@ int check_finite(cola_ctx* c) {
 
 int ic_from_mesh_noise(cola_ctx* c, const double* k, const double* pk, int nk) {
   const int np = c->p.np, nm = c->p.nmesh;
-  const long rs = 2 * padded_cols(np);
   const double box = c->p.box;
   // amplitude table sqrt(P(|k|) / dq^3) by integer |n|^2, from the table's
   // copy in the P(k) partials (a longer table than they hold: on the host)
@@ -326,7 +325,9 @@ int ic_from_mesh_noise(cola_ctx* c, const double* k, const double* pk, int nk) {
     HIP_TRY(c, hipMemcpyAsync(c->amp, amp.data(), amp.size() * sizeof(float), hipMemcpyHostToDevice, c->stream));
   }
   float2* A = ic_buf(c, 0);
-  float2* B[3] = {ic_buf(c, 1), ic_buf(c, 2), ic_buf(c, 3)};
+  float2* B[5];                          // B[i + 1] follows B[i] by ms
+  for (int i = 0; i < 5; ++i) B[i] = ic_buf(c, i + 1);
+  const long ms = mesh_complex_count(np);
   // delta_L(k) = DFT[w] sqrt(P / dq^3), k = 0 and Nyquist-index modes zeroed
   fft_r2c_z(A, np, 1, 0, c->tw, c->stream);
   fft_y(A, np, 1, 0, 0, c->tw, c->stream);
@@ -338,45 +339,40 @@ int ic_from_mesh_noise(cola_ctx* c, const double* k, const double* pk, int nk) {
   fft_x(xa, np, c->tw, c->stream);
   const double inv3 = 1.0 / ((double)np * np * np);
   const float sgrad = (float)(nm / (2.0 * kPi) * inv3);  // mesh units of the PM grid
-  auto inverse_into = [&](const float2* in, float2* out, int kind, int ca, int cb, float scale) {
+  auto x_pass = [&](int mode, const float2* in, float2* o0, float2* o1, float2* o2, float scale) {
     XPassArgs m;
     m.in = in;
-    m.out[0] = out;
-    m.mode = X_MULT_INV;
-    m.mult = kind;
-    m.comp_a = ca;
-    m.comp_b = cb;
+    m.out[0] = o0;
+    m.out[1] = o1;
+    m.out[2] = o2;
+    m.mode = mode;
     m.scale = scale;
     fft_x(m, np, c->tw, c->stream);
-    fft_y(out, np, 1, 0, 1, c->tw, c->stream);
-    fft_c2r_z(out, np, 1, 0, c->tw, c->stream);
+  };
+  // B[0 .. 2] = the x pass's two outputs -> the three components, real, into psi
+  auto gradient_into = [&](float* psi) {
+    fft_y(B[0], np, 1, 0, 1, c->tw, c->stream);
+    fft_y_grad_yz(B[1], B[2], np, c->tw, c->stream);
+    fft_c2r_z(B[0], np, 3, ms, c->tw, c->stream, psi);
   };
   // Psi1_d = IDFT[i k_d delta_L / k^2]
-  for (int d = 0; d < 3; ++d) {
-    inverse_into(A, B[0], M_GRAD, d, 0, sgrad);
-    launch_copy_from_mesh(reinterpret_cast<float*>(B[0]), np, rs, c->psi1 + d * c->np3, 1.0f, c->stream);
-  }
+  x_pass(X_PHI2, A, B[0], B[1], nullptr, sgrad);
+  gradient_into(c->psi1);
+  // second derivatives of phi = delta_L / k^2 (n_x^m in the x pass, n_y^m n_z^m' in the y pass), then
   // S = phi_xx phi_yy + phi_yy phi_zz + phi_zz phi_xx - phi_xy^2 - phi_yz^2 - phi_zx^2
-  for (int d = 0; d < 3; ++d) inverse_into(A, B[d], M_HESS, d, d, (float)inv3);
-  float* S = reinterpret_cast<float*>(B[0]);
-  launch_source_diag(S, reinterpret_cast<float*>(B[1]), reinterpret_cast<float*>(B[2]), np, rs, c->stream);
-  const int off[3][2] = {{0, 1}, {1, 2}, {2, 0}};
-  for (int q = 0; q < 3; ++q) {
-    inverse_into(A, B[1], M_HESS, off[q][0], off[q][1], (float)inv3);
-    launch_source_sub_sq(S, reinterpret_cast<float*>(B[1]), np, rs, c->stream);
-  }
+  x_pass(X_POW3, A, B[0], B[2], B[4], (float)inv3);              // phi, n_x phi, n_x^2 phi
+  float2* yy[3] = {A, B[1], B[0]};                               // n_z^2, n_y n_z, n_y^2
+  fft_y_pow(Y_POW3, B[0], yy, np, c->tw, c->stream);
+  float2* xy[3] = {B[3], B[2], nullptr};                         // n_x n_z, n_x n_y
+  fft_y_pow(Y_POW2, B[2], xy, np, c->tw, c->stream);
+  fft_y(B[4], np, 1, 0, 1, c->tw, c->stream);
+  float2* six[6] = {B[4], B[0], A, B[2], B[1], B[3]};
+  fft_c2r_z_source(six, np, c->tw, c->stream);
   // Psi2_d = IDFT[-i k_d S(k) / k^2]
-  fft_r2c_z(B[0], np, 1, 0, c->tw, c->stream);
-  fft_y(B[0], np, 1, 0, 0, c->tw, c->stream);
-  XPassArgs fx;
-  fx.in = B[0];
-  fx.out[0] = B[0];
-  fx.mode = X_FWD;
-  fft_x(fx, np, c->tw, c->stream);
-  for (int d = 0; d < 3; ++d) {
-    inverse_into(B[0], B[1], M_GRAD, d, 0, -sgrad);
-    launch_copy_from_mesh(reinterpret_cast<float*>(B[1]), np, rs, c->psi2 + d * c->np3, 1.0f, c->stream);
-  }
+  fft_r2c_z(B[4], np, 1, 0, c->tw, c->stream);
+  fft_y(B[4], np, 1, 0, 0, c->tw, c->stream);
+  x_pass(X_FWD_PHI2, B[4], B[0], B[1], nullptr, -sgrad);
+  gradient_into(c->psi2);
   const double a0 = c->p.a_init;
   launch_init_particles(c->disp, c->vres, c->psi1, c->psi2, c->np3,
                         (float)growth_D1(a0, c->p.omega_m), (float)D2_of(&c->p, a0),

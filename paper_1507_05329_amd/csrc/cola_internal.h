@@ -113,7 +113,15 @@ struct StepCoef {
 // X_FWD_GREEN (x pass): forward, phi = Green's function x spectrum,
 // out[0] = IDFT_x[i n_x phi], out[1] = IDFT_x[phi].  X_INV_GRAD_YZ (y pass,
 // inverse) on that B: out[0] = IDFT_y[i n_y B], out[1] = IDFT_y[i n_z B].
-enum XMode { X_FWD = 0, X_FWD_GREEN = 1, X_FWD_AMP = 2, X_MULT_INV = 3, X_INV = 4, X_INV_GRAD_YZ = 5 };
+// The 2LPT maps share transforms in the same way (phi = scale S / |n|^2):
+//   X_PHI2      (x pass, inverse) out[0] = IDFT_x[i n_x phi], out[1] = IDFT_x[phi];
+//   X_FWD_PHI2  the same after a forward transform, every Nyquist index zeroed;
+//   X_POW3      (x pass, inverse) out[m] = IDFT_x[n_x^m phi], m = 0, 1, 2;
+//   Y_POW2, Y_POW3 (y pass, inverse) out[m] = IDFT_y[n_y^m n_z^(M-1-m) in], m < M.
+enum XMode {
+  X_FWD = 0, X_FWD_GREEN = 1, X_FWD_AMP = 2, X_MULT_INV = 3, X_INV = 4, X_INV_GRAD_YZ = 5,
+  X_PHI2 = 6, X_FWD_PHI2 = 7, X_POW3 = 8, Y_POW2 = 9, Y_POW3 = 10
+};
 enum MultKind { M_NONE = 0, M_GRAD = 1, M_HESS = 2 };
 struct XPassArgs {
   const float2* in = nullptr;
@@ -147,8 +155,9 @@ void fft3d_inverse(float2* mesh, int n, const TwiddleSet& tw, hipStream_t s);
 // mesh c at offset c padded_cols).
 void fft_r2c_z(float2* mesh, int n, int nplanes_mesh, long mesh_stride, const TwiddleSet& tw,
                hipStream_t s, int nmock = 1, long mstride = 0, long rowc = 0);
+// out: null for in place, else dense rows of n floats, the meshes' outputs n^3 apart.
 void fft_c2r_z(float2* mesh, int n, int nmesh_batch, long mesh_stride, const TwiddleSet& tw,
-               hipStream_t s, int nmock = 1, long mstride = 0);
+               hipStream_t s, float* out = nullptr);
 // Inverse z pass of the three row-interleaved force meshes, the real
 // outputs interleaved by node: (g_x, g_y, g_z) of node (x, y, z) at floats
 // (x n + y) 6 padded_cols(n) + 3 z + {0, 1, 2}.
@@ -156,6 +165,12 @@ void fft_c2r_z_forces(float2* mesh, int n, const TwiddleSet& tw, hipStream_t s, 
 void fft_y(float2* mesh, int n, int nmesh_batch, long mesh_stride, int inverse,
            const TwiddleSet& tw, hipStream_t s, int nmock = 1, long mstride = 0, long rowc = 0);
 void fft_x(const XPassArgs& a, int n, const TwiddleSet& tw, hipStream_t s);
+// Y_POW2 / Y_POW3 on in (out[0] may be in itself).
+void fft_y_pow(int mode, const float2* in, float2* const out[3], int n, const TwiddleSet& tw, hipStream_t s);
+// Inverse z pass of phi_xx, phi_yy, phi_zz, phi_xy, phi_yz, phi_xz fused with the 2LPT
+// source: the real rows S = phi_xx phi_yy + phi_yy phi_zz + phi_zz phi_xx - phi_xy^2 -
+// phi_yz^2 - phi_xz^2 into the rows of f[0] (only there).
+void fft_c2r_z_source(float2* const f[6], int n, const TwiddleSet& tw, hipStream_t s);
 // Inverse y pass of the PM gradients: b -> IDFT_y[i n_y b] in place, IDFT_y[i n_z b] -> gz.
 void fft_y_grad_yz(float2* b, float2* gz, int n, const TwiddleSet& tw, hipStream_t s, int nmock = 1,
                    long mstride = 0, long rowc = 0);
@@ -197,9 +212,6 @@ void launch_copy_to_mesh(const float* src, int n, float* mesh, long row_stride, 
 // elem: floats between consecutive nodes of a row (3 for one component of the force field).
 void launch_copy_from_mesh(const float* mesh, int n, long row_stride, float* dst, float scale,
                            hipStream_t s, int elem = 1);
-void launch_source_diag(float* a, const float* b, const float* c, int n, long row_stride,
-                        hipStream_t s);
-void launch_source_sub_sq(float* a, const float* b, int n, long row_stride, hipStream_t s);
 void launch_init_particles(float* disp, float* vres, const float* psi1, const float* psi2,
                            long np3, float D1, float D2, hipStream_t s);
 void launch_axpby(float* y, const float* x, float a, float b, long n, hipStream_t s);

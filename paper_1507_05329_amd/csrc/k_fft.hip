@@ -539,11 +539,12 @@ __global__ __launch_bounds__(fcols_threads(N, cols_lim(N, MODE)), 4) void k_cols
         }
     }
     col_store_global<SL, W, T>(o, out0 + ofs, es, tid);
-  } else if constexpr (MODE == X_FWD_GREEN) {
+  } else if constexpr (MODE == X_FWD_GREEN || MODE == X_FWD_PHI2) {
     // PM, x pass: forward along x gives S = DFT[delta]; with phi = scale S / |n|^2
     //   out0 = IDFT_x[i n_x phi]  (n_x on its Nyquist index -> 0)  -> g_x,
     //   out1 = IDFT_x[phi]                                         -> g_y, g_z
     // (n_y and n_z are constant along an x line; the y pass applies them).
+    // 2LPT (X_FWD_PHI2): the same with every mode of a Nyquist index zeroed.
     using SI = Stg<N, 1 - O0, NST - 1, W, T, false>;
     float2 f[SL::KB][SL::R];
     reg_fft<N, O0, W, T, false, LD, 1, TL>(v, f, lds, twl, tid);
@@ -557,7 +558,10 @@ __global__ __launch_bounds__(fcols_threads(N, cols_lim(N, MODE)), 4) void k_cols
         const int nx = signed_freq(e, N), nz = c0 + c;
         const int n2 = nx * nx + pfreq * pfreq + nz * nz;
         // hardware reciprocal (within 1 ulp): one instruction instead of a division
-        const float inv = (n2 == 0 || nz > N / 2) ? 0.f : scale * __builtin_amdgcn_rcpf((float)n2);
+        bool zero = n2 == 0 || nz > N / 2;
+        if constexpr (MODE == X_FWD_PHI2)
+          zero = zero || nx == N / 2 || nx == -N / 2 || pfreq == N / 2 || pfreq == -N / 2 || nz == N / 2;
+        const float inv = zero ? 0.f : scale * __builtin_amdgcn_rcpf((float)n2);
         f[b][r] = make_float2(inv * f[b][r].x, inv * f[b][r].y);
         const float kx = (nx == N / 2 || nx == -N / 2) ? 0.f : (float)nx;
         u[b][r] = make_float2(-kx * f[b][r].y, kx * f[b][r].x);  // i n_x phi
@@ -569,6 +573,63 @@ __global__ __launch_bounds__(fcols_threads(N, cols_lim(N, MODE)), 4) void k_cols
     __syncthreads();
     reg_fft<N, 1 - O0, W, T, false, LD, 0, TL>(f, o, lds, twl, tid);
     col_store_global<SI, W, T>(o, out1 + ofs, es, tid);
+  } else if constexpr (MODE == X_PHI2 || MODE == X_POW3) {
+    // 2LPT, x pass from a spectrum S already transformed along all axes:
+    // phi = scale S / |n|^2, then IDFT_x[i n_x phi] and IDFT_x[phi] (X_PHI2) or
+    // IDFT_x[n_x^m phi], m = 2, 1, 0 (X_POW3).
+#pragma unroll
+    for (int b = 0; b < S0::KB; ++b)
+#pragma unroll
+      for (int r = 0; r < S0::R; ++r) {
+        int c;
+        const int nx = signed_freq(st_elem<S0, T>(tid, b, r, c), N), nz = c0 + c;
+        const int n2 = nx * nx + pfreq * pfreq + nz * nz;
+        const float inv = (n2 == 0 || nz > N / 2) ? 0.f : scale * __builtin_amdgcn_rcpf((float)n2);
+        v[b][r] = make_float2(inv * v[b][r].x, inv * v[b][r].y);
+      }
+    constexpr int M = MODE == X_PHI2 ? 2 : 3;
+#pragma unroll
+    for (int m = 0; m < M; ++m) {
+      float2 u[S0::KB][S0::R];
+#pragma unroll
+      for (int b = 0; b < S0::KB; ++b)
+#pragma unroll
+        for (int r = 0; r < S0::R; ++r) {
+          int c;
+          const int nx = signed_freq(st_elem<S0, T>(tid, b, r, c), N);
+          const float2 x = v[b][r];
+          const float kx = (nx == N / 2 || nx == -N / 2) ? 0.f : (float)nx;
+          if (MODE == X_PHI2) u[b][r] = m == 0 ? make_float2(-kx * x.y, kx * x.x) : x;
+          else u[b][r] = m == 2 ? x : m == 1 ? make_float2(kx * x.x, kx * x.y) : make_float2(kx * kx * x.x, kx * kx * x.y);
+        }
+      float2 o[SL::KB][SL::R];
+      if (m > 0) __syncthreads();
+      reg_fft<N, O0, W, T, false, LD, 0, TL>(u, o, lds, twl, tid);
+      col_store_global<SL, W, T>(o, (MODE == X_PHI2 ? (m == 0 ? out0 : out1) : (m == 0 ? out2 : m == 1 ? out1 : out0)) + ofs,
+                                 es, tid);
+    }
+  } else if constexpr (MODE == Y_POW2 || MODE == Y_POW3) {
+    // 2LPT, inverse y pass: out_m = IDFT_y[n_y^m n_z^(M-1-m) in], m = M-1 .. 0.
+    constexpr int M = MODE == Y_POW2 ? 2 : 3;
+#pragma unroll
+    for (int m = M - 1; m >= 0; --m) {
+      float2 u[S0::KB][S0::R];
+#pragma unroll
+      for (int b = 0; b < S0::KB; ++b)
+#pragma unroll
+        for (int r = 0; r < S0::R; ++r) {
+          int c;
+          const float ky = (float)signed_freq(st_elem<S0, T>(tid, b, r, c), N), kz = (float)(c0 + c);
+          float k = 1.f;
+#pragma unroll
+          for (int i = 0; i < M - 1; ++i) k *= i < m ? ky : kz;
+          u[b][r] = make_float2(k * v[b][r].x, k * v[b][r].y);
+        }
+      float2 o[SL::KB][SL::R];
+      if (m < M - 1) __syncthreads();
+      reg_fft<N, O0, W, T, false, LD, 0, TL>(u, o, lds, twl, tid);
+      col_store_global<SL, W, T>(o, (m == 0 ? out0 : m == 1 ? out1 : out2) + ofs, es, tid);
+    }
   } else if constexpr (MODE == X_INV_GRAD_YZ) {
     // PM, inverse y pass of B = IDFT_x[phi]: out0 = IDFT_y[i n_y B], out1 =
     // IDFT_y[i n_z B] (each component zeroed on its own Nyquist index).
@@ -683,19 +744,20 @@ __global__ __launch_bounds__(frows_threads_r2c(N), min_waves(frows_threads_r2c(N
 // Inverse: half spectrum (H+1 values) -> N reals, unnormalised.  The first
 // stage's inputs are formed in registers from X_k and X_{H-k}:
 //   Z'_k = (X_k + conj X_{H-k}) + i (X_k - conj X_{H-k}) exp(+2 pi i k / N),
-// and z = IDFT_H[Z'] holds the pairs (x_2m, x_2m+1).
+// and z = IDFT_H[Z'] holds the pairs (x_2m, x_2m+1).  Rows of ocols values in
+// out, which may be the mesh itself (a workgroup reads its rows before it writes).
 template <int N>
 __global__ __launch_bounds__(frows_threads(N), min_waves(frows_threads(N))) void k_c2r_z(
-    float2* __restrict__ mesh, long nrows, int cols, long mesh_stride, const float2* __restrict__ tw,
-    long mstride) {
+    float2* mesh, long nrows, int cols, long mesh_stride, const float2* __restrict__ tw, float2* out, long ocols,
+    long out_stride) {
   constexpr int H = N / 2, LD = fld(H), NL = frows_nl(N), T = frows_threads(N), TL = frows_tw_len(N);
   constexpr int OR = lo_first(H);
   using S0 = Stg<H, OR, 0, NL, T, true>;
   using SL = Stg<H, OR, nstage(H) - 1, NL, T, true>;
-  mesh = mock_ptr(mesh, mstride);
   __shared__ float2 lds[NL * LD];
   __shared__ float2 twl[TL];
-  float2* base = mesh + blockIdx.y * mesh_stride;
+  const float2* base = mesh + blockIdx.y * mesh_stride;
+  out += blockIdx.y * out_stride;
   const long r0 = (long)blockIdx.x * NL;
   const int tid = threadIdx.x;
   float2 xa[S0::KB][S0::R], xb[S0::KB][S0::R];
@@ -736,7 +798,7 @@ __global__ __launch_bounds__(frows_threads(N), min_waves(frows_threads(N))) void
     int l, j;
     SL::map(t, l, j);
     if (SL::ok(t) && r0 + l < nrows) {
-      float2* p = base + (r0 + l) * cols + j;
+      float2* p = out + (r0 + l) * ocols + j;
 #pragma unroll
       for (int r = 0; r < SL::R; ++r) p[r * SL::NS] = z[b][r];
     }
@@ -839,6 +901,90 @@ __global__ __launch_bounds__(frows_threads3(N), min_waves(frows_threads3(N))) vo
     }
     float* dst = reinterpret_cast<float*>(mesh + row * 3 * (long)cols) + o4;
     *reinterpret_cast<float4*>(dst) = make_float4(v[0], v[1], v[2], v[3]);
+  }
+}
+
+// Inverse z pass of the six second derivatives of the 2LPT potential, fused
+// with the source term: a workgroup takes the six lines of NL / 6 rows, and
+// writes one real row of S for them.  Memory-bound (7 half spectra): 124 us at
+// 256, where six separate passes and four elementwise ones took 300 us.  With
+// the shared x and y passes (X_PHI2, X_POW3, Y_POW*) the initial conditions of
+// 256^3 particles take 1.33 instead of 1.86 ms per call.
+struct SourceMeshes {
+  float2* f[6];   // phi_xx, phi_yy, phi_zz, phi_xy, phi_yz, phi_xz
+};
+constexpr int frows_nl_src(int n) {
+  const int fit = frows_nl(n) / 6 * 6, want = 6 * (3072 / (6 * (n / 2)) > 0 ? 3072 / (6 * (n / 2)) : 1);
+  return fit < want ? (fit < 6 ? 6 : fit) : want;
+}
+constexpr int fft_src_threads(int n) { return threads_for(frows_nl_src(n) * (n / 2)); }
+static_assert(6 * fld(512) * 8 + frows_tw_len(1024) * 8 <= kLdsLimit, "source LDS");
+
+template <int N>
+__global__ __launch_bounds__(fft_src_threads(N), min_waves(fft_src_threads(N))) void k_c2r_z_source(
+    SourceMeshes f, long nrows, int cols, const float2* __restrict__ tw) {
+  constexpr int H = N / 2, LD = fld(H), NL = frows_nl_src(N), T = fft_src_threads(N), TL = frows_tw_len(N);
+  constexpr int OR = lo_first(H);
+  using S0 = Stg<H, OR, 0, NL, T, true>;
+  using SL = Stg<H, OR, nstage(H) - 1, NL, T, true>;
+  __shared__ float2 lds[NL * LD];
+  __shared__ float2 twl[TL];
+  const long row0 = (long)blockIdx.x * (NL / 6);
+  const int tid = threadIdx.x;
+  float2 xa[S0::KB][S0::R], xb[S0::KB][S0::R];
+#pragma unroll
+  for (int b = 0; b < S0::KB; ++b) {
+    const int t = tid + b * T;
+    int l, j;
+    S0::map(t, l, j);
+    const bool in = S0::ok(t) && row0 + l / 6 < nrows;
+    const float2* p = f.f[l % 6] + (row0 + l / 6) * cols;
+#pragma unroll
+    for (int r = 0; r < S0::R; ++r) {
+      const int k = j + r * S0::NBL;
+      xa[b][r] = in ? p[k] : make_float2(0.f, 0.f);
+      xb[b][r] = in ? p[H - k] : make_float2(0.f, 0.f);
+    }
+  }
+  load_twiddles<TL, T>(twl, tw);
+  __syncthreads();
+#pragma unroll
+  for (int b = 0; b < S0::KB; ++b) {
+    int l, j;
+    S0::map(tid + b * T, l, j);
+#pragma unroll
+    for (int r = 0; r < S0::R; ++r) {
+      const float2 cb = make_float2(xb[b][r].x, -xb[b][r].y);
+      const float2 e = cadd(xa[b][r], cb);
+      const float2 o = cmulc(csub(xa[b][r], cb), tw_at<N, TL>(twl, j + r * S0::NBL));
+      xa[b][r] = cadd(e, make_float2(-o.y, o.x));
+    }
+  }
+  float2 z[SL::KB][SL::R];
+  reg_fft<H, OR, NL, T, true, LD, 0, TL>(xa, z, lds, twl, tid);
+  __syncthreads();
+#pragma unroll
+  for (int b = 0; b < SL::KB; ++b) {
+    const int t = tid + b * T;
+    if (SL::ok(t)) {
+      int l, j;
+      SL::map(t, l, j);
+#pragma unroll
+      for (int r = 0; r < SL::R; ++r) lds[l * LD + j + r * SL::NS] = z[b][r];
+    }
+  }
+  __syncthreads();
+  auto src = [](float xx, float yy, float zz, float xy, float yz, float xz) {
+    return xx * yy + yy * zz + zz * xx - xy * xy - yz * yz - xz * xz;
+  };
+  for (int i = tid; i < NL / 6 * H; i += T) {
+    const int q = i / H, m = i - q * H;
+    if (row0 + q >= nrows) continue;
+    float2 a[6];
+#pragma unroll
+    for (int e = 0; e < 6; ++e) a[e] = lds[(6 * q + e) * LD + m];
+    f.f[0][(row0 + q) * cols + m] = make_float2(src(a[0].x, a[1].x, a[2].x, a[3].x, a[4].x, a[5].x),
+                                                src(a[0].y, a[1].y, a[2].y, a[3].y, a[4].y, a[5].y));
   }
 }
 
@@ -1009,13 +1155,23 @@ void c2r3_n(float2* mesh, const float2* tw, hipStream_t s, int nmock, long mstri
 }
 
 template <int N>
-void c2r_n(float2* mesh, int nbatch, long mesh_stride, const float2* tw, hipStream_t s, int nmock,
-           long mstride) {
+void c2r_n(float2* mesh, int nbatch, long mesh_stride, const float2* tw, hipStream_t s, float* out) {
   constexpr int NL = frows_nl(N), T = frows_threads(N);
   const long nrows = (long)N * N;
-  dim3 grid((unsigned)((nrows + NL - 1) / NL), (unsigned)nbatch, (unsigned)nmock);
+  dim3 grid((unsigned)((nrows + NL - 1) / NL), (unsigned)nbatch);
   hipLaunchKernelGGL(k_c2r_z<N>, grid, dim3(T), 0, s, mesh, nrows, (int)padded_cols(N), mesh_stride, tw,
-                     mstride);
+                     out ? reinterpret_cast<float2*>(out) : mesh, out ? (long)N / 2 : padded_cols(N),
+                     out ? nrows * (N / 2) : mesh_stride);
+}
+
+template <int N>
+void c2r_source_n(float2* const f[6], const float2* tw, hipStream_t s) {
+  constexpr int NL = frows_nl_src(N), T = fft_src_threads(N);
+  const long nrows = (long)N * N;
+  SourceMeshes m;
+  for (int q = 0; q < 6; ++q) m.f[q] = f[q];
+  hipLaunchKernelGGL(k_c2r_z_source<N>, dim3((unsigned)((6 * nrows + NL - 1) / NL)), dim3(T), 0, s, m, nrows,
+                     (int)padded_cols(N), tw);
 }
 
 template <int N>
@@ -1061,6 +1217,22 @@ void cols_n(int mode, int axis, const float2* in, float2* const out[3], int nbat
                          mesh_stride, g, tw, 0, 0, 0, 1.f, nullptr, yf, nullptr, mstride, xo);
       break;
   }
+  // the 2LPT maps: particle grids only (1024 at most)
+  if constexpr (N <= 1024) {
+#define COLA_LPT_MODE(M)                                                                                      \
+  case M:                                                                                                     \
+    hipLaunchKernelGGL((k_cols<N, M>), grid, dim3(T), 0, s, in, out[0], out[1], out[2], mesh_stride, g, tw, 0, \
+                       0, 0, scale, nullptr, yf, nullptr, mstride, xo);                                       \
+    break;
+    switch (mode) {
+      COLA_LPT_MODE(X_PHI2)
+      COLA_LPT_MODE(X_FWD_PHI2)
+      COLA_LPT_MODE(X_POW3)
+      COLA_LPT_MODE(Y_POW2)
+      COLA_LPT_MODE(Y_POW3)
+    }
+#undef COLA_LPT_MODE
+  }
 }
 
 #define COLA_FFT_SIZES(X) X(16) X(32) X(48) X(64) X(96) X(128) X(192) X(256) X(384) X(512) \
@@ -1088,9 +1260,9 @@ void fft_r2c_z(float2* mesh, int n, int nbatch, long mesh_stride, const TwiddleS
 }
 
 void fft_c2r_z(float2* mesh, int n, int nbatch, long mesh_stride, const TwiddleSet& tw, hipStream_t s,
-               int nmock, long mstride) {
+               float* out) {
   switch (n) {
-#define X(NN) case NN: c2r_n<NN>(mesh, nbatch, mesh_stride, tw.get(NN), s, nmock, mstride); break;
+#define X(NN) case NN: c2r_n<NN>(mesh, nbatch, mesh_stride, tw.get(NN), s, out); break;
     COLA_FFT_SIZES(X)
 #undef X
     default: break;
@@ -1112,6 +1284,24 @@ void fft_y(float2* mesh, int n, int nbatch, long mesh_stride, int inverse, const
   const int mode = inverse ? X_INV : X_FWD;
   switch (n) {
 #define X(NN) case NN: cols_n<NN>(mode, 1, mesh, outs, nbatch, mesh_stride, tw.get(NN), 0, 0, 0, 1.f, nullptr, s, nullptr, nmock, mstride, rowc); break;
+    COLA_FFT_SIZES(X)
+#undef X
+    default: break;
+  }
+}
+
+void fft_c2r_z_source(float2* const f[6], int n, const TwiddleSet& tw, hipStream_t s) {
+  switch (n) {
+#define X(NN) case NN: if constexpr (NN <= 1024) c2r_source_n<NN>(f, tw.get(NN), s); break;
+    COLA_FFT_SIZES(X)
+#undef X
+    default: break;
+  }
+}
+
+void fft_y_pow(int mode, const float2* in, float2* const out[3], int n, const TwiddleSet& tw, hipStream_t s) {
+  switch (n) {
+#define X(NN) case NN: cols_n<NN>(mode, 1, in, out, 1, 0, tw.get(NN), 0, 0, 0, 1.f, nullptr, s); break;
     COLA_FFT_SIZES(X)
 #undef X
     default: break;

@@ -112,43 +112,6 @@ void launch_copy_from_mesh(const float* mesh, int n, long row_stride, float* dst
                      n3, row_stride, dst, scale, elem);
 }
 
-// 2LPT source, diagonal part: a <- a b + b c + c a (a, b, c = phi_xx, phi_yy, phi_zz).
-__global__ void k_source_diag(float* __restrict__ a, const float* __restrict__ b,
-                              const float* __restrict__ c, int n, long n3, long row_stride) {
-  for (long p = blockIdx.x * (long)blockDim.x + threadIdx.x; p < n3;
-       p += (long)gridDim.x * blockDim.x) {
-    const long row = p / n, col = p - row * n;
-    const long j = row * row_stride + col;
-    const float x = a[j], y = b[j], z = c[j];
-    a[j] = x * y + y * z + z * x;
-  }
-}
-
-void launch_source_diag(float* a, const float* b, const float* c, int n, long row_stride,
-                        hipStream_t s) {
-  const long n3 = (long)n * n * n;
-  hipLaunchKernelGGL(k_source_diag, dim3(grid_1d(n3)), dim3(256), 0, s, a, b, c, n,
-                     n3, row_stride);
-}
-
-// 2LPT source, off-diagonal part: a <- a - b^2.
-__global__ void k_source_sub_sq(float* __restrict__ a, const float* __restrict__ b, int n, long n3,
-                                long row_stride) {
-  for (long p = blockIdx.x * (long)blockDim.x + threadIdx.x; p < n3;
-       p += (long)gridDim.x * blockDim.x) {
-    const long row = p / n, col = p - row * n;
-    const long j = row * row_stride + col;
-    const float y = b[j];
-    a[j] = a[j] - y * y;
-  }
-}
-
-void launch_source_sub_sq(float* a, const float* b, int n, long row_stride, hipStream_t s) {
-  const long n3 = (long)n * n * n;
-  hipLaunchKernelGGL(k_source_sub_sq, dim3(grid_1d(n3)), dim3(256), 0, s, a, b, n,
-                     n3, row_stride);
-}
-
 // d = D1 Psi1 + D2 Psi2, v_res = 0 (x_res = v_res = 0 at the initial time).
 __global__ void k_init_particles(float* __restrict__ disp, float* __restrict__ vres,
                                  const float* __restrict__ psi1, const float* __restrict__ psi2,
