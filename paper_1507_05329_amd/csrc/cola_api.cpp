@@ -783,8 +783,8 @@ int cola_pk_velocity(cola_ctx* c, int32_t axis, const double* edges, int32_t nbi
   launch_los_weights(g, force_row_stride(nm), c->disp, c->vres, c->psi1, c->psi2, c->p.np, nm, k, axis,
                      (float)(1.0 / nbar), (float)(c->p.box / nm / (a * adot) / nbar), c->fbar, c->stream);
   tile_sort(c, nm, c->disp, false, true);
-  launch_deposit3_weighted(c->disp, c->perm, c->offsets, c->p.np, nm, c->fbar,
-                           reinterpret_cast<float*>(c->mesh[0]), rs, 2 * c->mesh_stride, c->stream);
+  launch_deposit_weighted(c->disp, c->perm, c->offsets, c->p.np, nm, c->fbar, 2, c->flag + 4,
+                          reinterpret_cast<float*>(c->mesh[0]), rs, 2 * c->mesh_stride, c->stream);
   fft3d_forward(c->mesh[0], nm, c->tw, c->stream);
   fft3d_forward(c->mesh[1], nm, c->tw, c->stream);
   launch_pk_cross(c->mesh[0], c->mesh[1], nm, c->p.box, c->pk_edges, nbins, axis, c->pk_partial, kPkChunks,
@@ -968,8 +968,8 @@ int step_adjoint(cola_ctx* c, double a0, double a1, double a_v0, const float* di
   launch_adj_readout_kick(disp0, g, force_row_stride(nm), np, nm, kd, dbar, vbar, p1bar, p2bar, c->fbar,
                           c->stream);
   // gbar_d = R^T Fbar_d (deterministic weighted deposit over the same sort)
-  launch_deposit3_weighted(disp0, c->perm, c->offsets, np, nm, c->fbar, gbar, rs, 2 * c->mesh_stride,
-                           c->stream);
+  launch_deposit_weighted(disp0, c->perm, c->offsets, np, nm, c->fbar, 3, c->flag + 4, gbar, rs, 2 * c->mesh_stride,
+                          c->stream);
   // rhobar = (Nm^3/Np) deltabar,  deltabar = -sum_d G_d gbar_d
   fft_r2c_z(c->mesh[0], nm, 3, c->mesh_stride, c->tw, c->stream);
   fft_y(c->mesh[0], nm, 3, c->mesh_stride, 0, c->tw, c->stream);

@@ -93,10 +93,11 @@ void launch_tile_sort(const float* disp, int np, int nm, float dscale, const Til
 // Deterministic CIC gather (k_deposit.hip).
 void launch_deposit(const float2* fxy, const float2* fzc, const uint32_t* off, int np, int nm, float* out,
                     long row_stride, int contrast, hipStream_t s, int nmock = 1, long mstride = 0);
-// Three weighted deposits at once (readout transpose): out[q] += sum_p wt[q][p] w_s(p).
-void launch_deposit3_weighted(const float* disp, const uint32_t* perm, const uint32_t* off, int np,
-                              int nm, const float* wt, float* out, long row_stride,
-                              long mesh_stride_floats, hipStream_t s);
+// Weighted deposits (readout transpose): out[q] = sum_p wt[q][p] w_s(p), q < ncomp
+// (2 or 3), with the ids of the tile sort; maxw: 3 words of scratch.
+void launch_deposit_weighted(const float* disp, const uint32_t* perm, const uint32_t* off, int np,
+                             int nm, const float* wt, int ncomp, uint32_t* maxw, float* out, long row_stride,
+                             long mesh_stride_floats, hipStream_t s);
 // Per-step scalars of the kick/drift and the Green pass.
 struct KickDrift {
   float K, c1, c2;     // v += K F - c1 Psi1 - c2 Psi2
@@ -245,7 +246,7 @@ void launch_halo_fill(const float* disp, const float* vel, const int32_t* lab, c
                       const uint32_t* flg, const uint32_t* hidx, int np, int nm, int nh, int stride,
                       unsigned long long* acc, int32_t* root, int32_t* cnt, float* pos, float* vout,
                       hipStream_t s);
-// Weights of that deposit (k_velocity.hip): 1/nbar, the scaled velocity along axis, 0.
+// Weights of that deposit (k_velocity.hip): 1/nbar, the scaled velocity along axis.
 void launch_los_weights(const float* g, long row_stride, const float* disp,
                         const float* vres, const float* psi1, const float* psi2, int np, int nm,
                         const VelCoef& k, int axis, float w0, float scale, float* wt, hipStream_t s);

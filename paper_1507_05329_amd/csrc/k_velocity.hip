@@ -104,7 +104,7 @@ void launch_snapshot(const float* g, long row_stride, const float* disp,
 
 // Weights of the density / line-of-sight momentum deposit: wt[0] = w0 (1/nbar),
 // wt[1] = scale * v_axis (the velocity of k_velocity, scaled to the shift per
-// particle over nbar), wt[2] = 0.
+// particle over nbar).
 template <bool KICK>
 __global__ __launch_bounds__(256) void k_los_weights(const float* __restrict__ g, long row_stride,
                                                      const float* __restrict__ disp, const float* __restrict__ vres,
@@ -126,7 +126,6 @@ __global__ __launch_bounds__(256) void k_los_weights(const float* __restrict__ g
   const float v = vres[j] + k.K * F + k.u1 * psi1[j] + k.u2 * psi2[j];
   wt[i] = w0;
   wt[np3 + i] = scale * v;
-  wt[2 * np3 + i] = 0.f;
 }
 
 void launch_los_weights(const float* g, long row_stride, const float* disp,

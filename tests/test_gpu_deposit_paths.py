@@ -14,7 +14,8 @@ pytestmark = pytest.mark.gpu
 
 torch = pytest.importorskip("torch")
 
-from oracle import cic_fp32  # noqa: E402
+from oracle import adjoint, cic_fp32, cola, ic  # noqa: E402
+from paper_1507_05329_amd.inputs import bbks_table, seeded_normal, step_edges, white_noise  # noqa: E402
 
 
 def faces(np_side, nm, seed, crowd):
@@ -89,3 +90,56 @@ def test_non_finite_displacements_leave_the_other_particles():
     mass = (got.astype(np.float64) + 1.0).sum() * np_side ** 3 / nm ** 3
     assert abs(mass - (np_side ** 3 - 3)) < 1e-3
     assert np.isfinite(keep).all()
+
+
+def adjoint_of(np_side, nm, seed, edit=None):
+    """One adjoint step from a state after two steps, and the oracle's."""
+    from paper_1507_05329_amd.sim import ColaSim
+    box, e = 3.0 * np_side, step_edges()
+    sim = ColaSim(np_side, nm, box)
+    try:
+        sim.init_from_noise(torch.from_numpy(white_noise(seed, np_side)).cuda(), *bbks_table())
+        sim.run(e[:3])
+        st = sim.get_state()
+        db, vb = (seeded_normal(seed + k, (3, np_side ** 3)) for k in (1, 2))
+        if edit:
+            edit(db, vb)
+        out = [torch.from_numpy(db).cuda(), torch.from_numpy(vb).cuda()]
+        out += [torch.zeros_like(out[0]), torch.zeros_like(out[0])]
+        sim.step_adjoint(e[2], e[3], st["a_v"], st["disp"], *out)
+        got = [x.cpu().numpy().astype(np.float64) for x in out]
+    finally:
+        sim.close()
+    s = box / nm
+    h = {n: st[n].cpu().numpy().astype(np.float64) * s for n in ("disp", "vres", "psi1", "psi2")}
+    o = cola.State(np_side, nm, box, 0.27, -2.5, ic.lattice(np_side, box), h["disp"], h["vres"], h["psi1"], h["psi2"],
+                   st["a_x"], st["a_v"])
+    return got, [x * s for x in adjoint.step_adjoint(o, e[3], db / s, vb / s)] if edit is None else None
+
+
+@pytest.mark.parametrize("np_side,nm", [(32, 32), (48, 48), (64, 64), (16, 96), (48, 128)])
+def test_weighted_deposit_in_the_adjoint_step(np_side, nm):
+    say(f"[gpu] adjoint step {np_side}^3 / {nm}^3")
+    got, ref = adjoint_of(np_side, nm, np_side)
+    for g, r in zip(got, ref):
+        assert np.linalg.norm(g - r) / np.linalg.norm(r) < 1e-4
+
+
+def test_weights_of_any_size():
+    # cotangents 1e-30 and 1e30 times as large give results 1e-30 and 1e30 times as large; one that
+    # is not finite leaves none finite of what depends on the transforms, and the others untouched
+    say("[gpu] weighted deposit of small, large and non-finite weights")
+    base, _ = adjoint_of(32, 64, 9, lambda db, vb: None)
+    for f in (2.0 ** -100, 2.0 ** 90):
+        def scale(db, vb):
+            db *= np.float32(f)
+            vb *= np.float32(f)
+        got, _ = adjoint_of(32, 64, 9, scale)
+        for g, r in zip(got, base):
+            assert np.linalg.norm(g / f - r) / np.linalg.norm(r) < 1e-5
+    for bad in (np.inf, np.nan):
+        def spoil(db, vb):
+            vb[1, 77] = bad
+        got, _ = adjoint_of(32, 64, 9, spoil)
+        assert not np.isfinite(got[0]).any()
+        assert np.isfinite(np.delete(got[1], 77, axis=1)).all() and not np.isfinite(got[1][1, 77])
