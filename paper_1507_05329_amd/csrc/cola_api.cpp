@@ -80,7 +80,7 @@ Layout layout(const cola_params* p) {
   const long nt = p->nmesh / 16;           // 16^3-cell tiles of the deposit
   L.nbucket = 8 * nt * nt * nt;
   L.mesh_stride = mesh_complex_count(p->nmesh);
-  const long pm = 3 * L.mesh_stride, ic = 6 * mesh_complex_count(p->np);  // IC adjoint: 6 meshes
+  const long pm = 3 * L.mesh_stride, ic = 7 * mesh_complex_count(p->np);  // IC adjoint: 7 meshes
   L.mesh_region = pm > ic ? pm : ic;
   L.amp_len = 3L * (p->np / 2) * (p->np / 2) + 1;
   L.tw_cap = p->nmesh > p->np ? p->nmesh : p->np;
@@ -307,6 +307,28 @@ int check_finite(cola_ctx* c) {
   return COLA_OK;
 }
 
+// Second derivatives of phi = scale delta_L / |n|^2 up to the z transform, from
+// the spectrum of delta_L in A (overwritten): n_x^m in the x pass, n_y^m n_z^m'
+// in the y pass.  six = xx, yy, zz, xy, yz, xz in the meshes A, B[0 .. 4].
+void hessian_xy(cola_ctx* c, float2* A, float2* const B[5], float scale, float2* six[6]) {
+  const int np = c->p.np;
+  XPassArgs m;
+  m.in = A;
+  m.out[0] = B[0];       // phi
+  m.out[1] = B[2];       // n_x phi
+  m.out[2] = B[4];       // n_x^2 phi
+  m.mode = X_POW3;
+  m.scale = scale;
+  fft_x(m, np, c->tw, c->stream);
+  float2* yy[3] = {A, B[1], B[0]};                               // n_z^2, n_y n_z, n_y^2
+  fft_y_pow(Y_POW3, B[0], yy, np, c->tw, c->stream);
+  float2* xy[3] = {B[3], B[2], nullptr};                         // n_x n_z, n_x n_y
+  fft_y_pow(Y_POW2, B[2], xy, np, c->tw, c->stream);
+  fft_y(B[4], np, 1, 0, 1, c->tw, c->stream);
+  float2* s[6] = {B[4], B[0], A, B[2], B[1], B[3]};
+  for (int q = 0; q < 6; ++q) six[q] = s[q];
+}
+
 int ic_from_mesh_noise(cola_ctx* c, const double* k, const double* pk, int nk) {
   const int np = c->p.np, nm = c->p.nmesh;
   const double box = c->p.box;
@@ -339,12 +361,11 @@ int ic_from_mesh_noise(cola_ctx* c, const double* k, const double* pk, int nk) {
   fft_x(xa, np, c->tw, c->stream);
   const double inv3 = 1.0 / ((double)np * np * np);
   const float sgrad = (float)(nm / (2.0 * kPi) * inv3);  // mesh units of the PM grid
-  auto x_pass = [&](int mode, const float2* in, float2* o0, float2* o1, float2* o2, float scale) {
+  auto x_pass = [&](int mode, const float2* in, float2* o0, float2* o1, float scale) {
     XPassArgs m;
     m.in = in;
     m.out[0] = o0;
     m.out[1] = o1;
-    m.out[2] = o2;
     m.mode = mode;
     m.scale = scale;
     fft_x(m, np, c->tw, c->stream);
@@ -356,22 +377,16 @@ int ic_from_mesh_noise(cola_ctx* c, const double* k, const double* pk, int nk) {
     fft_c2r_z(B[0], np, 3, ms, c->tw, c->stream, psi);
   };
   // Psi1_d = IDFT[i k_d delta_L / k^2]
-  x_pass(X_PHI2, A, B[0], B[1], nullptr, sgrad);
+  x_pass(X_PHI2, A, B[0], B[1], sgrad);
   gradient_into(c->psi1);
-  // second derivatives of phi = delta_L / k^2 (n_x^m in the x pass, n_y^m n_z^m' in the y pass), then
   // S = phi_xx phi_yy + phi_yy phi_zz + phi_zz phi_xx - phi_xy^2 - phi_yz^2 - phi_zx^2
-  x_pass(X_POW3, A, B[0], B[2], B[4], (float)inv3);              // phi, n_x phi, n_x^2 phi
-  float2* yy[3] = {A, B[1], B[0]};                               // n_z^2, n_y n_z, n_y^2
-  fft_y_pow(Y_POW3, B[0], yy, np, c->tw, c->stream);
-  float2* xy[3] = {B[3], B[2], nullptr};                         // n_x n_z, n_x n_y
-  fft_y_pow(Y_POW2, B[2], xy, np, c->tw, c->stream);
-  fft_y(B[4], np, 1, 0, 1, c->tw, c->stream);
-  float2* six[6] = {B[4], B[0], A, B[2], B[1], B[3]};
+  float2* six[6];
+  hessian_xy(c, A, B, (float)inv3, six);
   fft_c2r_z_source(six, np, c->tw, c->stream);
   // Psi2_d = IDFT[-i k_d S(k) / k^2]
   fft_r2c_z(B[4], np, 1, 0, c->tw, c->stream);
   fft_y(B[4], np, 1, 0, 0, c->tw, c->stream);
-  x_pass(X_FWD_PHI2, B[4], B[0], B[1], nullptr, -sgrad);
+  x_pass(X_FWD_PHI2, B[4], B[0], B[1], -sgrad);
   gradient_into(c->psi2);
   const double a0 = c->p.a_init;
   launch_init_particles(c->disp, c->vres, c->psi1, c->psi2, c->np3,
@@ -936,6 +951,23 @@ int cola_fft3d(cola_ctx* c, int32_t n, float* mesh, int32_t inverse) {
 // Adjoint.
 
 namespace {
+// Forward y passes of the three components of a vector field (z transforms
+// done; component d at m + d stride): the x component alone, i n_y times the y
+// component plus i n_z times the z component into the y component's mesh; adds
+// scale (i n_x x-component + that sum) to the x pass's combination.
+void divergence_xy(cola_ctx* c, float2* m, long stride, int n, float scale, CombineSpec* cs) {
+  fft_y(m, n, 1, 0, 0, c->tw, c->stream);
+  YCombine yc;
+  yc.nin = 2;
+  yc.in[0] = m + stride;
+  yc.in[1] = m + 2 * stride;
+  yc.py[0] = yc.pz[1] = 1;
+  yc.imag[0] = yc.imag[1] = 1;
+  fft_combine_y(yc, m + stride, n, c->tw, c->stream);
+  cs->add(m, 1, 1, scale);
+  cs->add(m + stride, 0, 0, scale);
+}
+
 // Adjoint of one step.  kept: the step's force meshes left by
 // cola_step_keep (three meshes mesh_stride apart), or null to recompute them.
 int step_adjoint(cola_ctx* c, double a0, double a1, double a_v0, const float* disp0, const float2* kept,
@@ -972,15 +1004,10 @@ int step_adjoint(cola_ctx* c, double a0, double a1, double a_v0, const float* di
                           c->stream);
   // rhobar = (Nm^3/Np) deltabar,  deltabar = -sum_d G_d gbar_d
   fft_r2c_z(c->mesh[0], nm, 3, c->mesh_stride, c->tw, c->stream);
-  fft_y(c->mesh[0], nm, 3, c->mesh_stride, 0, c->tw, c->stream);
-  CombineSpec cs;
-  cs.nin = 3;
-  cs.green = 1;
-  const double gscale = green_scale(nm, alpha);
   const double cratio = (double)nm * nm * nm / (double)c->np3;
-  cs.scale = (float)(-gscale * cratio);
-  const float2* ins[3] = {c->mesh[0], c->mesh[1], c->mesh[2]};
-  fft_combine_x(ins, c->mesh[0], nm, cs, nullptr, c->tw, c->stream);
+  CombineSpec cs;
+  divergence_xy(c, c->mesh[0], c->mesh_stride, nm, (float)(-green_scale(nm, alpha) * cratio), &cs);
+  fft_combine_x(cs, c->mesh[0], nm, nullptr, c->tw, c->stream);
   fft_y(c->mesh[0], nm, 1, 0, 1, c->tw, c->stream);
   fft_c2r_z(c->mesh[0], nm, 1, 0, c->tw, c->stream);
   launch_adj_deposit_grad(disp0, gbar, rs, np, nm, 1.0f, 1.0f, dbar, c->stream);
@@ -1071,85 +1098,62 @@ int cola_init_2lpt_adjoint(cola_ctx* c, const float* noise, const float* dbar0, 
   const float D1 = (float)growth_D1(a0, om), D2 = (float)D2_of(&c->p, a0);
   const double inv3 = 1.0 / ((double)np * np * np);
   const float sgrad = (float)(nm / (2.0 * kPi) * inv3);
-  float2* C0 = ic_buf(c, 0);
-  float2* S = ic_buf(c, 1);
-  float2* B = ic_buf(c, 2);   // B, B + ms, B + 2 ms
-  float2* Wb = ic_buf(c, 5);
-  auto fwd_zy3 = [&](float2* m) {
-    fft_r2c_z(m, np, 3, ms, c->tw, c->stream);
-    fft_y(m, np, 3, ms, 0, c->tw, c->stream);
-  };
-  auto inv_zy = [&](float2* m) {
-    fft_y(m, np, 1, 0, 1, c->tw, c->stream);
-    fft_c2r_z(m, np, 1, 0, c->tw, c->stream);
-  };
-  const float2* Bs[3] = {B, B + ms, B + 2 * ms};
+  // the second derivatives as the initial conditions lay them out, and Sbar
+  float2* A = ic_buf(c, 0);
+  float2* B[5];
+  for (int i = 0; i < 5; ++i) B[i] = ic_buf(c, i + 1);
+  float2* S = ic_buf(c, 6);
   // Sbar = IDFT[sum_d conj(M2_d) DFT(Psi2bar_d)], conj(M2_d) = +i n_d sg / |n|^2
-  launch_axpy_to_mesh(p2bar, dbar0, D2, np, reinterpret_cast<float*>(B), rs, 2 * ms, c->stream);
-  fwd_zy3(B);
-  CombineSpec cs;
-  cs.nin = 3;
-  cs.scale = sgrad;
-  fft_combine_x(Bs, S, np, cs, nullptr, c->tw, c->stream);
-  inv_zy(S);
-  // delta_L spectrum from the noise
-  launch_copy_to_mesh(noise, np, reinterpret_cast<float*>(C0), rs, c->stream);
-  fft_r2c_z(C0, np, 1, 0, c->tw, c->stream);
-  fft_y(C0, np, 1, 0, 0, c->tw, c->stream);
+  launch_axpy_to_mesh(p2bar, dbar0, D2, np, reinterpret_cast<float*>(B[0]), rs, 2 * ms, c->stream);
+  fft_r2c_z(B[0], np, 3, ms, c->tw, c->stream);
+  CombineSpec gs;
+  gs.nyq = 1;
+  divergence_xy(c, B[0], ms, np, sgrad, &gs);
+  fft_combine_x(gs, S, np, nullptr, c->tw, c->stream);
+  fft_y(S, np, 1, 0, 1, c->tw, c->stream);
+  fft_c2r_z(S, np, 1, 0, c->tw, c->stream);
+  // delta_L spectrum from the noise, its second derivatives up to the z transform
+  launch_copy_to_mesh(noise, np, reinterpret_cast<float*>(A), rs, c->stream);
+  fft_r2c_z(A, np, 1, 0, c->tw, c->stream);
+  fft_y(A, np, 1, 0, 0, c->tw, c->stream);
   XPassArgs xa;
-  xa.in = C0;
-  xa.out[0] = C0;
+  xa.in = A;
+  xa.out[0] = A;
   xa.mode = X_FWD_AMP;
   xa.amp = c->amp;
   fft_x(xa, np, c->tw, c->stream);
-  auto phi_into = [&](float2* out, int i, int j) {
-    XPassArgs m;
-    m.in = C0;
-    m.out[0] = out;
-    m.mode = X_MULT_INV;
-    m.mult = M_HESS;
-    m.comp_a = i;
-    m.comp_b = j;
-    m.scale = (float)inv3;
-    fft_x(m, np, c->tw, c->stream);
-    inv_zy(out);
-  };
-  // diagonal phi_ii -> phibar_ii, then wbar += IDFT[A n_i n_i / n^2 / np^3 DFT(phibar_ii)]
-  for (int d = 0; d < 3; ++d) phi_into(B + d * ms, d, d);
-  launch_phibar_diag(reinterpret_cast<float*>(B), reinterpret_cast<float*>(B + ms),
-                     reinterpret_cast<float*>(B + 2 * ms), reinterpret_cast<float*>(S), np, rs, c->stream);
-  fwd_zy3(B);
-  CombineSpec hs;
-  hs.nin = 3;
-  hs.kind[0] = hs.kind[1] = hs.kind[2] = M_HESS;
-  hs.ca[0] = 0; hs.cb[0] = 0;
-  hs.ca[1] = 1; hs.cb[1] = 1;
-  hs.ca[2] = 2; hs.cb[2] = 2;
-  hs.scale = (float)inv3;
-  hs.use_amp = 1;
-  fft_combine_x(Bs, Wb, np, hs, c->amp, c->tw, c->stream);
-  // off-diagonal
-  const int od[3][2] = {{0, 1}, {1, 2}, {2, 0}};
-  for (int q = 0; q < 3; ++q) phi_into(B + q * ms, od[q][0], od[q][1]);
-  launch_phibar_off(reinterpret_cast<float*>(B), reinterpret_cast<float*>(S), np, rs, 2 * ms, c->stream);
-  fwd_zy3(B);
-  for (int q = 0; q < 3; ++q) {
-    hs.ca[q] = od[q][0];
-    hs.cb[q] = od[q][1];
-  }
-  hs.accumulate = 1;
-  fft_combine_x(Bs, Wb, np, hs, c->amp, c->tw, c->stream);
-  // Psi1: wbar += IDFT[A conj(M1_d) DFT(Psi1bar_d)], conj(M1_d) = -i n_d sg / |n|^2
-  launch_axpy_to_mesh(p1bar, dbar0, D1, np, reinterpret_cast<float*>(B), rs, 2 * ms, c->stream);
-  fwd_zy3(B);
-  CombineSpec gs;
-  gs.nin = 3;
-  gs.scale = -sgrad;
-  gs.use_amp = 1;
-  gs.accumulate = 1;
-  fft_combine_x(Bs, Wb, np, gs, c->amp, c->tw, c->stream);
-  inv_zy(Wb);
-  launch_copy_from_mesh(reinterpret_cast<float*>(Wb), np, rs, noise_bar, 1.0f, c->stream);
+  float2* six[6];
+  hessian_xy(c, A, B, (float)inv3, six);
+  // phi_ij -> phibar_ij along z, then wbar = IDFT[A sum_ij n_i n_j / n^2 / np^3 DFT(phibar_ij)]
+  fft_phibar_z(six, S, np, c->tw, c->stream);
+  fft_y(six[0], np, 1, 0, 0, c->tw, c->stream);            // xx
+  YCombine y2, y1;
+  y2.nin = 3;                                              // n_y^2 yy + n_y n_z yz + n_z^2 zz
+  y2.in[0] = six[1];
+  y2.in[1] = six[4];
+  y2.in[2] = six[2];
+  y2.py[0] = 2;
+  y2.py[1] = y2.pz[1] = 1;
+  y2.pz[2] = 2;
+  fft_combine_y(y2, six[1], np, c->tw, c->stream);
+  y1.nin = 2;                                              // n_y xy + n_z xz
+  y1.in[0] = six[3];
+  y1.in[1] = six[5];
+  y1.py[0] = y1.pz[1] = 1;
+  fft_combine_y(y1, six[3], np, c->tw, c->stream);
+  CombineSpec ws;
+  ws.nyq = ws.use_amp = 1;
+  ws.add(six[0], 2, 0, (float)inv3);
+  ws.add(six[3], 1, 0, (float)inv3);
+  ws.add(six[1], 0, 0, (float)inv3);
+  // Psi1: wbar += IDFT[A conj(M1_d) DFT(Psi1bar_d)], conj(M1_d) = -i n_d sg / |n|^2,
+  // in the three meshes two apart that are free again (zz, yz, xz)
+  launch_axpy_to_mesh(p1bar, dbar0, D1, np, reinterpret_cast<float*>(A), rs, 4 * ms, c->stream);
+  fft_r2c_z(A, np, 3, 2 * ms, c->tw, c->stream);
+  divergence_xy(c, A, 2 * ms, np, -sgrad, &ws);
+  fft_combine_x(ws, S, np, c->amp, c->tw, c->stream);
+  fft_y(S, np, 1, 0, 1, c->tw, c->stream);
+  fft_c2r_z(S, np, 1, 0, c->tw, c->stream, noise_bar);
   LAUNCH_CHECK(c, "cola_init_2lpt_adjoint");
   return COLA_OK;
 }

@@ -120,35 +120,46 @@ struct StepCoef {
 //   X_POW3      (x pass, inverse) out[m] = IDFT_x[n_x^m phi], m = 0, 1, 2;
 //   Y_POW2, Y_POW3 (y pass, inverse) out[m] = IDFT_y[n_y^m n_z^(M-1-m) in], m < M.
 enum XMode {
-  X_FWD = 0, X_FWD_GREEN = 1, X_FWD_AMP = 2, X_MULT_INV = 3, X_INV = 4, X_INV_GRAD_YZ = 5,
+  X_FWD = 0, X_FWD_GREEN = 1, X_FWD_AMP = 2, X_INV = 4, X_INV_GRAD_YZ = 5,
   X_PHI2 = 6, X_FWD_PHI2 = 7, X_POW3 = 8, Y_POW2 = 9, Y_POW3 = 10
 };
-enum MultKind { M_NONE = 0, M_GRAD = 1, M_HESS = 2 };
 struct XPassArgs {
   const float2* in = nullptr;
   float2* out[3] = {nullptr, nullptr, nullptr};
   int mode = X_FWD;
-  int mult = M_NONE;
-  int comp_a = 0, comp_b = 0;   // gradient axis / Hessian axes
-  float scale = 1.f;            // multiplier scale
+  float scale = 1.f;            // scale of phi
   const float* amp = nullptr;   // amplitude by integer |n|^2 (X_FWD_AMP)
   const StepCoef* coef = nullptr;  // X_FWD_GREEN: scale read from coef->gscale
   int nmock = 1;                // batched mocks (blockIdx.z) ...
   long mstride = 0;             // ... at this byte stride
   long rowc = 0;                // row stride in complex values (0: padded_cols(n))
 };
-// Spectral combination pass (adjoint): out = IDFT_x[sum_q m_q DFT_x(in_q)].
+// Spectral combinations of the adjoint (k_fft.hip: k_ycomb, k_combine).
+struct YCombine {
+  int nin = 0;
+  const float2* in[3] = {nullptr, nullptr, nullptr};
+  int py[3] = {0, 0, 0}, pz[3] = {0, 0, 0}, imag[3] = {0, 0, 0};   // i^imag n_y^py n_z^pz
+};
 struct CombineSpec {
   int nin = 0;
-  int kind[3] = {M_GRAD, M_GRAD, M_GRAD};
-  int ca[3] = {0, 1, 2}, cb[3] = {0, 0, 0};
-  float scale = 1.f;
-  int green = 0;        // 1: a gradient is zeroed only on its own axis' Nyquist plane
-  int use_amp = 0;      // multiply by the amplitude table (all Nyquist modes zeroed)
-  int accumulate = 0;   // out += result
+  const float2* in[5] = {nullptr, nullptr, nullptr, nullptr, nullptr};
+  int px[5] = {0, 0, 0, 0, 0}, imag[5] = {0, 0, 0, 0, 0};          // scale i^imag n_x^px
+  float scale[5] = {0.f, 0.f, 0.f, 0.f, 0.f};
+  int nyq = 0;          // 1: every mode of a Nyquist index zeroed
+  int use_amp = 0;      // multiply by the amplitude table
+  void add(const float2* p, int power, int im, float s) {
+    in[nin] = p;
+    px[nin] = power;
+    imag[nin] = im;
+    scale[nin++] = s;
+  }
 };
-void fft_combine_x(const float2* const in[3], float2* out, int n, const CombineSpec& cs,
-                   const float* amp, const TwiddleSet& tw, hipStream_t s);
+// out may be one of the inputs.
+void fft_combine_x(const CombineSpec& cs, float2* out, int n, const float* amp, const TwiddleSet& tw, hipStream_t s);
+void fft_combine_y(const YCombine& yc, float2* out, int n, const TwiddleSet& tw, hipStream_t s);
+// Inverse z transforms of phi_xx, phi_yy, phi_zz, phi_xy, phi_yz, phi_xz, the cotangents of the
+// 2LPT source with Sbar (real rows) for each, and their forward z transforms, in place.
+void fft_phibar_z(float2* const f[6], const float2* sbar, int n, const TwiddleSet& tw, hipStream_t s);
 void fft3d_forward(float2* mesh, int n, const TwiddleSet& tw, hipStream_t s);
 void fft3d_inverse(float2* mesh, int n, const TwiddleSet& tw, hipStream_t s);
 // rowc: row stride in complex values (0: padded_cols(n)); the PM force
@@ -258,10 +269,6 @@ void launch_adj_deposit_grad(const float* disp, const float* field, long row_str
                              float dscale, float coef, float* dbar, hipStream_t s);
 void launch_axpy_to_mesh(const float* a, const float* b, float alpha, int n, float* mesh,
                          long row_stride, long mesh_stride_floats, hipStream_t s);
-void launch_phibar_diag(float* a, float* b, float* c, const float* sbar, int n, long row_stride,
-                        hipStream_t s);
-void launch_phibar_off(float* a, const float* sbar, int n, long row_stride, long mesh_stride_floats,
-                       hipStream_t s);
 void launch_pk_adj_modes(const float2* X, float2* Z, int ng, double box, const double* edges,
                          int nbins, const double* cbar, const double* sums, hipStream_t s);
 // Non-finite check.

@@ -131,45 +131,4 @@ void launch_axpy_to_mesh(const float* a, const float* b, float alpha, int n, flo
                      n, n3, mesh, row_stride, mesh_stride_floats);
 }
 
-// 2LPT source adjoint (S = pxx pyy + pyy pzz + pzz pxx - pxy^2 - pyz^2 - pzx^2):
-// diagonal: (a, b, c) <- Sbar (b + c, a + c, a + b); off-diagonal: a <- -2 Sbar a.
-__global__ void k_phibar_diag(float* __restrict__ a, float* __restrict__ b, float* __restrict__ c,
-                              const float* __restrict__ sbar, int n, long n3, long row_stride) {
-  for (long p = blockIdx.x * (long)blockDim.x + threadIdx.x; p < n3;
-       p += (long)gridDim.x * blockDim.x) {
-    const long row = p / n, col = p - row * n;
-    const long j = row * row_stride + col;
-    const float x = a[j], y = b[j], z = c[j], sb = sbar[j];
-    a[j] = sb * (y + z);
-    b[j] = sb * (x + z);
-    c[j] = sb * (x + y);
-  }
-}
-
-__global__ void k_phibar_off(float* __restrict__ a, const float* __restrict__ sbar, int n, long n3,
-                             long row_stride, long mesh_stride) {
-  for (long p = blockIdx.x * (long)blockDim.x + threadIdx.x; p < n3;
-       p += (long)gridDim.x * blockDim.x) {
-    const long row = p / n, col = p - row * n;
-    const long j = row * row_stride + col;
-    const float sb = sbar[j];
-  #pragma unroll
-    for (int q = 0; q < 3; ++q) a[q * mesh_stride + j] = -2.0f * sb * a[q * mesh_stride + j];
-  }
-}
-
-void launch_phibar_diag(float* a, float* b, float* c, const float* sbar, int n, long row_stride,
-                        hipStream_t s) {
-  const long n3 = (long)n * n * n;
-  hipLaunchKernelGGL(k_phibar_diag, dim3(grid_1d(n3)), dim3(256), 0, s, a, b, c, sbar,
-                     n, n3, row_stride);
-}
-
-void launch_phibar_off(float* a, const float* sbar, int n, long row_stride, long mesh_stride_floats,
-                       hipStream_t s) {
-  const long n3 = (long)n * n * n;
-  hipLaunchKernelGGL(k_phibar_off, dim3(grid_1d(n3)), dim3(256), 0, s, a, sbar, n, n3,
-                     row_stride, mesh_stride_floats);
-}
-
 }  // namespace cola

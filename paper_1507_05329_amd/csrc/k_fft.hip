@@ -179,33 +179,11 @@ struct ColGeom {
 
 __device__ __forceinline__ int signed_freq(int i, int n) { return i <= n / 2 ? i : i - n; }
 
-// k-space multiplier for mode (nx, ny, nz); rfft axis nz in [0, n/2].
-__device__ __forceinline__ float2 multiplier(int kind, int green, int ca, int cb, float scale,
-                                             int nx, int ny, int nz, int n,
-                                             const float* __restrict__ amp, int is_amp) {
-  const int h = n / 2;
-  if (nz > h) return make_float2(0.f, 0.f);
-  const int ax = nx < 0 ? -nx : nx, ay = ny < 0 ? -ny : ny;
-  const int n2 = nx * nx + ny * ny + nz * nz;
-  if (n2 == 0) return make_float2(0.f, 0.f);
-  const bool nyq = ax == h || ay == h || nz == h;
-  if (is_amp) {
-    if (nyq) return make_float2(0.f, 0.f);
-    return make_float2(amp[n2], 0.f);
-  }
-  if (kind == M_GRAD) {
-    const int na = ca == 0 ? nx : (ca == 1 ? ny : nz);
-    const int aa = na < 0 ? -na : na;
-    if (green ? (aa == h) : nyq) return make_float2(0.f, 0.f);
-    return make_float2(0.f, scale * (float)na / (float)n2);
-  }
-  if (kind == M_HESS) {
-    if (nyq) return make_float2(0.f, 0.f);
-    const int na = ca == 0 ? nx : (ca == 1 ? ny : nz);
-    const int nb = cb == 0 ? nx : (cb == 1 ? ny : nz);
-    return make_float2(scale * (float)na * (float)nb / (float)n2, 0.f);
-  }
-  return make_float2(1.f, 0.f);
+// Amplitude of mode (nx, ny, nz); 0 at k = 0, at every Nyquist index and in the row padding.
+__device__ __forceinline__ float amplitude(int nx, int ny, int nz, int n, const float* __restrict__ amp) {
+  const int h = n / 2, n2 = nx * nx + ny * ny + nz * nz;
+  const bool zero = n2 == 0 || nz >= h || nx == h || nx == -h || ny == h || ny == -h;
+  return zero ? 0.f : amp[n2];
 }
 
 // ---------------------------------------------------------------------------
@@ -478,7 +456,7 @@ constexpr int kPlainOrd = 1;
 template <int N, int MODE>
 __global__ __launch_bounds__(fcols_threads(N, cols_lim(N, MODE)), 4) void k_cols(
     const float2* __restrict__ in, float2* out0, float2* out1, float2* out2, long mesh_stride,
-    ColGeom g, const float2* __restrict__ tw, int mult, int ca, int cb, float scale,
+    ColGeom g, const float2* __restrict__ tw, float scale,
     const float* __restrict__ amp, int y_is_plane_freq, const StepCoef* __restrict__ coef,
     long mstride, int xcd_order) {
   in = mock_ptr(in, mstride);
@@ -514,18 +492,7 @@ __global__ __launch_bounds__(fcols_threads(N, cols_lim(N, MODE)), 4) void k_cols
   col_load_global<S0, W, T>(v, in + ofs, es, tid);
   load_twiddles<TL, T>(twl, tw);
 
-  if constexpr (MODE == X_FWD || MODE == X_INV || MODE == X_FWD_AMP || MODE == X_MULT_INV) {
-    if constexpr (MODE == X_MULT_INV) {
-#pragma unroll
-      for (int b = 0; b < S0::KB; ++b)
-#pragma unroll
-        for (int r = 0; r < S0::R; ++r) {
-          int c;
-          const int e = st_elem<S0, T>(tid, b, r, c);
-          v[b][r] = cmul(v[b][r], multiplier(mult, 0, ca, cb, scale, signed_freq(e, N), pfreq, c0 + c, N,
-                                             amp, 0));
-        }
-    }
+  if constexpr (MODE == X_FWD || MODE == X_INV || MODE == X_FWD_AMP) {
     float2 o[SL::KB][SL::R];
     reg_fft<N, O0, W, T, false, LD, (MODE == X_FWD || MODE == X_FWD_AMP) ? 1 : 0, TL>(v, o, lds, twl, tid);
     if constexpr (MODE == X_FWD_AMP) {
@@ -535,7 +502,8 @@ __global__ __launch_bounds__(fcols_threads(N, cols_lim(N, MODE)), 4) void k_cols
         for (int r = 0; r < SL::R; ++r) {
           int c;
           const int e = st_elem<SL, T>(tid, b, r, c);
-          o[b][r] = cmul(o[b][r], multiplier(0, 0, 0, 0, 0.f, signed_freq(e, N), pfreq, c0 + c, N, amp, 1));
+          const float m = amplitude(signed_freq(e, N), pfreq, c0 + c, N, amp);
+          o[b][r] = make_float2(m * o[b][r].x, m * o[b][r].y);
         }
     }
     col_store_global<SL, W, T>(o, out0 + ofs, es, tid);
@@ -920,18 +888,14 @@ constexpr int frows_nl_src(int n) {
 constexpr int fft_src_threads(int n) { return threads_for(frows_nl_src(n) * (n / 2)); }
 static_assert(6 * fld(512) * 8 + frows_tw_len(1024) * 8 <= kLdsLimit, "source LDS");
 
-template <int N>
-__global__ __launch_bounds__(fft_src_threads(N), min_waves(fft_src_threads(N))) void k_c2r_z_source(
-    SourceMeshes f, long nrows, int cols, const float2* __restrict__ tw) {
-  constexpr int H = N / 2, LD = fld(H), NL = frows_nl_src(N), T = fft_src_threads(N), TL = frows_tw_len(N);
-  constexpr int OR = lo_first(H);
+// First-stage inputs of the inverse z transform of the workgroup's lines (line l:
+// mesh l mod 6, row row0 + l / 6), as in k_c2r_z; loads the twiddles.
+template <int N, int NL, int T, int TL, int OR, class A0>
+__device__ __forceinline__ void src_lines_in(A0& xa, const SourceMeshes& f, long row0, long nrows, int cols, float2* twl,
+                                             const float2* __restrict__ tw, int tid) {
+  constexpr int H = N / 2;
   using S0 = Stg<H, OR, 0, NL, T, true>;
-  using SL = Stg<H, OR, nstage(H) - 1, NL, T, true>;
-  __shared__ float2 lds[NL * LD];
-  __shared__ float2 twl[TL];
-  const long row0 = (long)blockIdx.x * (NL / 6);
-  const int tid = threadIdx.x;
-  float2 xa[S0::KB][S0::R], xb[S0::KB][S0::R];
+  float2 xb[S0::KB][S0::R];
 #pragma unroll
   for (int b = 0; b < S0::KB; ++b) {
     const int t = tid + b * T;
@@ -960,9 +924,11 @@ __global__ __launch_bounds__(fft_src_threads(N), min_waves(fft_src_threads(N))) 
       xa[b][r] = cadd(e, make_float2(-o.y, o.x));
     }
   }
-  float2 z[SL::KB][SL::R];
-  reg_fft<H, OR, NL, T, true, LD, 0, TL>(xa, z, lds, twl, tid);
-  __syncthreads();
+}
+
+// Last-stage outputs in natural order: element e of line l at lds[l LD + e].
+template <class SL, int T, int LD>
+__device__ __forceinline__ void lines_to_lds(const float2 (&z)[SL::KB][SL::R], float2* lds, int tid) {
 #pragma unroll
   for (int b = 0; b < SL::KB; ++b) {
     const int t = tid + b * T;
@@ -973,6 +939,25 @@ __global__ __launch_bounds__(fft_src_threads(N), min_waves(fft_src_threads(N))) 
       for (int r = 0; r < SL::R; ++r) lds[l * LD + j + r * SL::NS] = z[b][r];
     }
   }
+}
+
+template <int N>
+__global__ __launch_bounds__(fft_src_threads(N), min_waves(fft_src_threads(N))) void k_c2r_z_source(
+    SourceMeshes f, long nrows, int cols, const float2* __restrict__ tw) {
+  constexpr int H = N / 2, LD = fld(H), NL = frows_nl_src(N), T = fft_src_threads(N), TL = frows_tw_len(N);
+  constexpr int OR = lo_first(H);
+  using S0 = Stg<H, OR, 0, NL, T, true>;
+  using SL = Stg<H, OR, nstage(H) - 1, NL, T, true>;
+  __shared__ float2 lds[NL * LD];
+  __shared__ float2 twl[TL];
+  const long row0 = (long)blockIdx.x * (NL / 6);
+  const int tid = threadIdx.x;
+  float2 xa[S0::KB][S0::R];
+  src_lines_in<N, NL, T, TL, OR>(xa, f, row0, nrows, cols, twl, tw, tid);
+  float2 z[SL::KB][SL::R];
+  reg_fft<H, OR, NL, T, true, LD, 0, TL>(xa, z, lds, twl, tid);
+  __syncthreads();
+  lines_to_lds<SL, T, LD>(z, lds, tid);
   __syncthreads();
   auto src = [](float xx, float yy, float zz, float xy, float yz, float xz) {
     return xx * yy + yy * zz + zz * xx - xy * xy - yz * yz - xz * xz;
@@ -988,19 +973,153 @@ __global__ __launch_bounds__(fft_src_threads(N), min_waves(fft_src_threads(N))) 
   }
 }
 
-// x pass of a spectral combination: out = IDFT_x[ sum_q m_q(k) DFT_x(in_q) ]
-// for inputs already transformed along z and y (so m_q sees the full k).
-// m_q is the gradient (i n_d scale / |n|^2) or Hessian (n_a n_b scale / |n|^2)
-// multiplier, optionally times the amplitude table; accumulate adds the result
-// to out instead of overwriting it.  Used by the adjoint (transposed Green's
-// function and transposed 2LPT maps).  Each input's forward transform ends
-// in registers, where the multiplied spectra are summed; the inverse
-// transform starts from that sum (mirrored radix orders).
+// Adjoint of the 2LPT source, along z: the inverse transforms of the six second
+// derivatives, their cotangents
+//   phibar_xx = Sbar (phi_yy + phi_zz) (cyclic),  phibar_xy = -2 Sbar phi_xy (...),
+// and the forward transforms of those, in place, row by row: 12 half spectra and
+// one real mesh moved instead of 37 (128^3: 33 us).
 template <int N>
-__global__ __launch_bounds__(fcols_threads(N), 4) void k_combine(
-    const float2* __restrict__ in0, const float2* __restrict__ in1, const float2* __restrict__ in2,
-    float2* out, ColGeom g, const float2* __restrict__ tw, CombineSpec cs,
-    const float* __restrict__ amp) {
+__global__ __launch_bounds__(fft_src_threads(N), min_waves(fft_src_threads(N))) void k_phibar_z(
+    SourceMeshes f, const float2* __restrict__ sbar, long nrows, int cols, const float2* __restrict__ tw) {
+  constexpr int H = N / 2, LD = fld(H), NL = frows_nl_src(N), T = fft_src_threads(N), TL = frows_tw_len(N);
+  constexpr int OR = lo_first(H);
+  using S0 = Stg<H, OR, 0, NL, T, true>;
+  using SL = Stg<H, OR, nstage(H) - 1, NL, T, true>;
+  __shared__ float2 lds[NL * LD];
+  __shared__ float2 twl[TL];
+  const long row0 = (long)blockIdx.x * (NL / 6);
+  const int tid = threadIdx.x;
+  {
+    float2 v[S0::KB][S0::R];
+    src_lines_in<N, NL, T, TL, OR>(v, f, row0, nrows, cols, twl, tw, tid);
+    float2 z[SL::KB][SL::R];
+    reg_fft<H, OR, NL, T, true, LD, 0, TL>(v, z, lds, twl, tid);
+    __syncthreads();
+    lines_to_lds<SL, T, LD>(z, lds, tid);
+  }
+  __syncthreads();
+  for (int i = tid; i < NL / 6 * H; i += T) {
+    const int q = i / H, m = i - q * H;
+    if (row0 + q >= nrows) continue;
+    const float2 sb = sbar[(row0 + q) * cols + m];
+    float2* p = lds + 6 * q * LD + m;
+    const float2 xx = p[0], yy = p[LD], zz = p[2 * LD];
+    p[0] = make_float2(sb.x * (yy.x + zz.x), sb.y * (yy.y + zz.y));
+    p[LD] = make_float2(sb.x * (xx.x + zz.x), sb.y * (xx.y + zz.y));
+    p[2 * LD] = make_float2(sb.x * (xx.x + yy.x), sb.y * (xx.y + yy.y));
+#pragma unroll
+    for (int e = 3; e < 6; ++e) {
+      const float2 x = p[e * LD];
+      p[e * LD] = make_float2(-2.0f * sb.x * x.x, -2.0f * sb.y * x.y);
+    }
+  }
+  __syncthreads();
+  {
+    float2 v[S0::KB][S0::R];
+#pragma unroll
+    for (int b = 0; b < S0::KB; ++b) {
+      const int t = tid + b * T;
+      if (S0::ok(t)) {
+        int l, j;
+        S0::map(t, l, j);
+#pragma unroll
+        for (int r = 0; r < S0::R; ++r) v[b][r] = lds[l * LD + j + r * S0::NBL];
+      }
+    }
+    __syncthreads();
+    float2 z[SL::KB][SL::R];
+    reg_fft<H, OR, NL, T, true, LD, 1, TL>(v, z, lds, twl, tid);
+    __syncthreads();
+    lines_to_lds<SL, T, LD>(z, lds, tid);
+  }
+  __syncthreads();
+  // the split step of k_r2c_z
+  constexpr int COLS = pcols(N);
+  for (int i = tid; i < NL * COLS; i += T) {
+    const int l = i / COLS, k = i - l * COLS;
+    if (row0 + l / 6 >= nrows) continue;
+    float2 x = make_float2(0.f, 0.f);
+    if (k <= H) {
+      const float2 a = lds[l * LD + (k == H ? 0 : k)];
+      float2 c = lds[l * LD + (k == 0 ? 0 : H - k)];
+      c.y = -c.y;
+      const float2 e = make_float2(0.5f * (a.x + c.x), 0.5f * (a.y + c.y));
+      const float2 o = make_float2(0.5f * (a.y - c.y), -0.5f * (a.x - c.x));
+      x = cadd(e, cmul(tw_at<N, TL>(twl, k), o));
+    }
+    f.f[l % 6][(row0 + l / 6) * cols + k] = x;
+  }
+}
+
+// Adjoint combinations (transposed Green's function and 2LPT maps): sums of
+// spectra over the components of a gradient or the elements of a Hessian,
+// factor by factor: what depends on n_y and n_z is applied and summed in the
+// forward y pass, what depends on n_x in the x pass, 1 / |n|^2 there once.  For
+// a divergence that is 5 + 3 half spectra moved instead of 6 + 4 with one x
+// transform per component (768 mesh: y passes 2.33 -> 2.21 ms, x pass 2.66 ->
+// 1.88 ms); for the 2LPT maps of 128^3 particles 0.46 -> 0.22 ms in all.
+//
+// Forward y pass: out = sum_q i^(imag_q) n_y^(py_q) n_z^(pz_q) DFT_y(in_q).
+template <int N>
+__global__ __launch_bounds__(fcols_threads(N), 4) void k_ycomb(YCombine yc, float2* out, ColGeom g,
+                                                               const float2* __restrict__ tw) {
+  constexpr int W = fcols_w(N), LD = fcols_ld(N), T = fcols_threads(N), TL = ftw_len(N);
+  constexpr int NST = nstage(N), OF = kPlainOrd;
+  using S0 = Stg<N, OF, 0, W, T, false>;
+  using SL = Stg<N, OF, NST - 1, W, T, false>;
+  __shared__ float2 lds[W * LD];
+  __shared__ float2 twl[TL];
+  const uint32_t nblk = (uint32_t)g.nchunk * g.nplanes;
+  const uint32_t bid = xcd_remap(blockIdx.x, nblk);
+  const int p = bid / g.nchunk;
+  const int c0 = (bid - p * g.nchunk) * W;
+  const long es = g.elem_stride, ofs = (long)p * g.plane_stride + c0;
+  const int tid = threadIdx.x;
+  load_twiddles<TL, T>(twl, tw);
+  float2 acc[SL::KB][SL::R];
+#pragma unroll
+  for (int b = 0; b < SL::KB; ++b)
+#pragma unroll
+    for (int r = 0; r < SL::R; ++r) acc[b][r] = make_float2(0.f, 0.f);
+#pragma unroll 1
+  for (int q = 0; q < yc.nin; ++q) {
+    // a thread index the compiler cannot treat as loop-invariant, so the
+    // transform's address arithmetic is not hoisted out and kept live
+    const int qt = opaque_tid();
+    float2 v[S0::KB][S0::R];
+    col_load_global<S0, W, T>(v, yc.in[q] + ofs, es, qt);
+    if (q > 0) __syncthreads();  // the previous transform's last LDS reads are done
+    float2 f[SL::KB][SL::R];
+    reg_fft<N, OF, W, T, false, LD, 1, TL>(v, f, lds, twl, qt);
+    const int py = yc.py[q], pz = yc.pz[q], imag = yc.imag[q];
+#pragma unroll
+    for (int b = 0; b < SL::KB; ++b)
+#pragma unroll
+      for (int r = 0; r < SL::R; ++r) {
+        int c;
+        const int ny = signed_freq(st_elem<SL, T>(qt, b, r, c), N), nz = c0 + c;
+        // a first derivative is zero on its own axis' Nyquist plane
+        const float ky = imag && (ny == N / 2 || ny == -N / 2) ? 0.f : (float)ny;
+        const float kz = imag && nz == N / 2 ? 0.f : (float)nz;
+        float m = py == 0 ? 1.f : py == 1 ? ky : ky * ky;
+        m *= pz == 0 ? 1.f : pz == 1 ? kz : kz * kz;
+        const float2 x = f[b][r];
+        acc[b][r] = cadd(acc[b][r], imag ? make_float2(-m * x.y, m * x.x) : make_float2(m * x.x, m * x.y));
+      }
+  }
+  col_store_global<SL, W, T>(acc, out + ofs, es, tid);
+}
+
+// x pass: out = IDFT_x[ amp / |n|^2 sum_q scale_q i^(imag_q) n_x^(px_q) DFT_x(in_q) ],
+// amp = 1 without the amplitude table (use_amp), k = 0 -> 0; nyq: every mode
+// of a Nyquist index -> 0 (else a first derivative on its own axis only).
+// Each input's forward transform ends in registers, where the multiplied
+// spectra are summed; the inverse transform starts from that sum (mirrored
+// radix orders).
+template <int N>
+__global__ __launch_bounds__(fcols_threads(N), 4) void k_combine(CombineSpec cs, float2* out, ColGeom g,
+                                                                 const float2* __restrict__ tw,
+                                                                 const float* __restrict__ amp) {
   constexpr int W = fcols_w(N), LD = fcols_ld(N), T = fcols_threads(N), TL = ftw_len(N);
   constexpr int NST = nstage(N), OF = lo_first(N);
   using S0 = Stg<N, OF, 0, W, T, false>;
@@ -1015,71 +1134,52 @@ __global__ __launch_bounds__(fcols_threads(N), 4) void k_combine(
   const int pfreq = signed_freq(p, N);
   const long es = g.elem_stride, ofs = (long)p * g.plane_stride + c0;
   const int tid = threadIdx.x;
-  const int h = N / 2;
+  constexpr int h = N / 2;
   load_twiddles<TL, T>(twl, tw);
   float2 acc[SL::KB][SL::R];
 #pragma unroll
   for (int b = 0; b < SL::KB; ++b)
 #pragma unroll
     for (int r = 0; r < SL::R; ++r) acc[b][r] = make_float2(0.f, 0.f);
-  const float2* ins[3] = {in0, in1, in2};
 #pragma unroll 1
   for (int q = 0; q < cs.nin; ++q) {
-    // a thread index the compiler cannot treat as loop-invariant, so the
-    // transform's address arithmetic is not hoisted out and kept live
     const int qt = opaque_tid();
     float2 v[S0::KB][S0::R];
-    col_load_global<S0, W, T>(v, ins[q] + ofs, es, qt);
+    col_load_global<S0, W, T>(v, cs.in[q] + ofs, es, qt);
     if (q > 0) __syncthreads();  // the previous transform's last LDS reads are done
     float2 f[SL::KB][SL::R];
     reg_fft<N, OF, W, T, false, LD, 1, TL>(v, f, lds, twl, qt);
-    const int kind = cs.kind[q], ca = cs.ca[q], cb = cs.cb[q];
+    const int px = cs.px[q], imag = cs.imag[q];
+    const float scale = cs.scale[q];
 #pragma unroll
     for (int b = 0; b < SL::KB; ++b)
 #pragma unroll
       for (int r = 0; r < SL::R; ++r) {
         int c;
-        const int e = st_elem<SL, T>(qt, b, r, c);
-        const int nx = signed_freq(e, N), nz = c0 + c;
-        const int na = ca == 0 ? nx : (ca == 1 ? pfreq : nz);
-        const bool nyq = nx == h || nx == -h || pfreq == h || pfreq == -h || nz == h;
-        // scale / |n|^2 (times the amplitude), recomputed per input rather
-        // than held in registers across the inputs (hardware reciprocal)
-        const int n2 = nx * nx + pfreq * pfreq + nz * nz;
-        const float rw = (n2 != 0 && nz <= h && !(cs.use_amp && nyq))
-                             ? cs.scale * __builtin_amdgcn_rcpf((float)n2) * (cs.use_amp ? amp[n2] : 1.f)
-                             : 0.f;
+        const int nx = signed_freq(st_elem<SL, T>(qt, b, r, c), N);
+        const float kx = imag && (nx == h || nx == -h) ? 0.f : (float)nx;
+        const float m = scale * (px == 0 ? 1.f : px == 1 ? kx : kx * kx);
         const float2 x = f[b][r];
-        if (kind == M_GRAD) {
-          // i n_a rw; zero on the axis' own Nyquist plane (Green) or any Nyquist index
-          const bool z = cs.green ? (na == h || na == -h) : nyq;
-          const float m = z ? 0.f : (float)na * rw;
-          acc[b][r] = cadd(acc[b][r], make_float2(-m * x.y, m * x.x));
-        } else {
-          const int nb = cb == 0 ? nx : (cb == 1 ? pfreq : nz);
-          const float m = nyq ? 0.f : (float)na * (float)nb * rw;
-          acc[b][r] = cadd(acc[b][r], make_float2(m * x.x, m * x.y));
-        }
+        acc[b][r] = cadd(acc[b][r], imag ? make_float2(-m * x.y, m * x.x) : make_float2(m * x.x, m * x.y));
       }
   }
+#pragma unroll
+  for (int b = 0; b < SL::KB; ++b)
+#pragma unroll
+    for (int r = 0; r < SL::R; ++r) {
+      int c;
+      const int nx = signed_freq(st_elem<SL, T>(tid, b, r, c), N), nz = c0 + c;
+      const int n2 = nx * nx + pfreq * pfreq + nz * nz;
+      const bool nyq = nx == h || nx == -h || pfreq == h || pfreq == -h || nz == h;
+      const bool zero = n2 == 0 || nz > h || (cs.nyq && nyq);
+      // hardware reciprocal (within 1 ulp): one instruction instead of a division
+      const float w = zero ? 0.f : __builtin_amdgcn_rcpf((float)n2) * (cs.use_amp ? amp[n2] : 1.f);
+      acc[b][r] = make_float2(w * acc[b][r].x, w * acc[b][r].y);
+    }
   __syncthreads();
   float2 o[SI::KB][SI::R];
   reg_fft<N, 1 - OF, W, T, false, LD, 0, TL>(acc, o, lds, twl, tid);
-  float2* dst = out + ofs;
-#pragma unroll
-  for (int b = 0; b < SI::KB; ++b) {
-    const int t = tid + b * T;
-    if (SI::ok(t)) {
-      int c, j;
-      SI::map(t, c, j);
-      float2* pd = dst + (long)j * es + c;
-#pragma unroll
-      for (int r = 0; r < SI::R; ++r) {
-        float2* e = pd + (long)r * SI::NS * es;
-        *e = cs.accumulate ? cadd(*e, o[b][r]) : o[b][r];
-      }
-    }
-  }
+  col_store_global<SI, W, T>(o, out + ofs, es, tid);
 }
 
 // ---------------------------------------------------------------------------
@@ -1175,8 +1275,18 @@ void c2r_source_n(float2* const f[6], const float2* tw, hipStream_t s) {
 }
 
 template <int N>
+void phibar_n(float2* const f[6], const float2* sbar, const float2* tw, hipStream_t s) {
+  constexpr int NL = frows_nl_src(N), T = fft_src_threads(N);
+  const long nrows = (long)N * N;
+  SourceMeshes m;
+  for (int q = 0; q < 6; ++q) m.f[q] = f[q];
+  hipLaunchKernelGGL(k_phibar_z<N>, dim3((unsigned)((6 * nrows + NL - 1) / NL)), dim3(T), 0, s, m, sbar, nrows,
+                     (int)padded_cols(N), tw);
+}
+
+template <int N>
 void cols_n(int mode, int axis, const float2* in, float2* const out[3], int nbatch, long mesh_stride,
-            const float2* tw, int mult, int ca, int cb, float scale, const float* amp, hipStream_t s,
+            const float2* tw, float scale, const float* amp, hipStream_t s,
             const StepCoef* coef = nullptr, int nmock = 1, long mstride = 0, long rowc = 0) {
   constexpr int LG = cols_lim(N, X_FWD_GREEN);
   const int W = mode == X_FWD_GREEN ? fcols_w(N, LG) : fcols_w(N);
@@ -1194,35 +1304,31 @@ void cols_n(int mode, int axis, const float2* in, float2* const out[3], int nbat
   switch (mode) {
     case X_FWD:
       hipLaunchKernelGGL((k_cols<N, X_FWD>), grid, dim3(T), 0, s, in, out[0], nullptr, nullptr,
-                         mesh_stride, g, tw, 0, 0, 0, 1.f, nullptr, yf, nullptr, mstride, xo);
+                         mesh_stride, g, tw, 1.f, nullptr, yf, nullptr, mstride, xo);
       break;
     case X_INV:
       hipLaunchKernelGGL((k_cols<N, X_INV>), grid, dim3(T), 0, s, in, out[0], nullptr, nullptr,
-                         mesh_stride, g, tw, 0, 0, 0, 1.f, nullptr, yf, nullptr, mstride, xo);
+                         mesh_stride, g, tw, 1.f, nullptr, yf, nullptr, mstride, xo);
       break;
     case X_FWD_AMP:
       hipLaunchKernelGGL((k_cols<N, X_FWD_AMP>), grid, dim3(T), 0, s, in, out[0], nullptr, nullptr,
-                         mesh_stride, g, tw, 0, 0, 0, 1.f, amp, yf, nullptr, mstride, xo);
-      break;
-    case X_MULT_INV:
-      hipLaunchKernelGGL((k_cols<N, X_MULT_INV>), grid, dim3(T), 0, s, in, out[0], nullptr, nullptr,
-                         mesh_stride, g, tw, mult, ca, cb, scale, nullptr, yf, nullptr, mstride, xo);
+                         mesh_stride, g, tw, 1.f, amp, yf, nullptr, mstride, xo);
       break;
     case X_FWD_GREEN:
       hipLaunchKernelGGL((k_cols<N, X_FWD_GREEN>), grid, dim3(T), 0, s, in, out[0], out[1], nullptr,
-                         mesh_stride, g, tw, M_GRAD, 0, 0, scale, nullptr, yf, coef, mstride, xo);
+                         mesh_stride, g, tw, scale, nullptr, yf, coef, mstride, xo);
       break;
     case X_INV_GRAD_YZ:
       hipLaunchKernelGGL((k_cols<N, X_INV_GRAD_YZ>), grid, dim3(T), 0, s, in, out[0], out[1], nullptr,
-                         mesh_stride, g, tw, 0, 0, 0, 1.f, nullptr, yf, nullptr, mstride, xo);
+                         mesh_stride, g, tw, 1.f, nullptr, yf, nullptr, mstride, xo);
       break;
   }
   // the 2LPT maps: particle grids only (1024 at most)
   if constexpr (N <= 1024) {
 #define COLA_LPT_MODE(M)                                                                                      \
   case M:                                                                                                     \
-    hipLaunchKernelGGL((k_cols<N, M>), grid, dim3(T), 0, s, in, out[0], out[1], out[2], mesh_stride, g, tw, 0, \
-                       0, 0, scale, nullptr, yf, nullptr, mstride, xo);                                       \
+    hipLaunchKernelGGL((k_cols<N, M>), grid, dim3(T), 0, s, in, out[0], out[1], out[2], mesh_stride, g, tw,    \
+                       scale, nullptr, yf, nullptr, mstride, xo);                                             \
     break;
     switch (mode) {
       COLA_LPT_MODE(X_PHI2)
@@ -1283,7 +1389,7 @@ void fft_y(float2* mesh, int n, int nbatch, long mesh_stride, int inverse, const
   float2* outs[3] = {mesh, nullptr, nullptr};
   const int mode = inverse ? X_INV : X_FWD;
   switch (n) {
-#define X(NN) case NN: cols_n<NN>(mode, 1, mesh, outs, nbatch, mesh_stride, tw.get(NN), 0, 0, 0, 1.f, nullptr, s, nullptr, nmock, mstride, rowc); break;
+#define X(NN) case NN: cols_n<NN>(mode, 1, mesh, outs, nbatch, mesh_stride, tw.get(NN), 1.f, nullptr, s, nullptr, nmock, mstride, rowc); break;
     COLA_FFT_SIZES(X)
 #undef X
     default: break;
@@ -1299,9 +1405,18 @@ void fft_c2r_z_source(float2* const f[6], int n, const TwiddleSet& tw, hipStream
   }
 }
 
+void fft_phibar_z(float2* const f[6], const float2* sbar, int n, const TwiddleSet& tw, hipStream_t s) {
+  switch (n) {
+#define X(NN) case NN: if constexpr (NN <= 1024) phibar_n<NN>(f, sbar, tw.get(NN), s); break;
+    COLA_FFT_SIZES(X)
+#undef X
+    default: break;
+  }
+}
+
 void fft_y_pow(int mode, const float2* in, float2* const out[3], int n, const TwiddleSet& tw, hipStream_t s) {
   switch (n) {
-#define X(NN) case NN: cols_n<NN>(mode, 1, in, out, 1, 0, tw.get(NN), 0, 0, 0, 1.f, nullptr, s); break;
+#define X(NN) case NN: cols_n<NN>(mode, 1, in, out, 1, 0, tw.get(NN), 1.f, nullptr, s); break;
     COLA_FFT_SIZES(X)
 #undef X
     default: break;
@@ -1312,7 +1427,7 @@ void fft_y_grad_yz(float2* b, float2* gz, int n, const TwiddleSet& tw, hipStream
                    long mstride, long rowc) {
   float2* outs[3] = {b, gz, nullptr};
   switch (n) {
-#define X(NN) case NN: cols_n<NN>(X_INV_GRAD_YZ, 1, b, outs, 1, 0, tw.get(NN), 0, 0, 0, 1.f, nullptr, s, nullptr, nmock, mstride, rowc); break;
+#define X(NN) case NN: cols_n<NN>(X_INV_GRAD_YZ, 1, b, outs, 1, 0, tw.get(NN), 1.f, nullptr, s, nullptr, nmock, mstride, rowc); break;
     COLA_FFT_SIZES(X)
 #undef X
     default: break;
@@ -1322,7 +1437,7 @@ void fft_y_grad_yz(float2* b, float2* gz, int n, const TwiddleSet& tw, hipStream
 void fft_x(const XPassArgs& a, int n, const TwiddleSet& tw, hipStream_t s) {
   float2* outs[3] = {a.out[0], a.out[1], a.out[2]};
   switch (n) {
-#define X(NN) case NN: cols_n<NN>(a.mode, 0, a.in, outs, 1, 0, tw.get(NN), a.mult, a.comp_a, a.comp_b, a.scale, a.amp, s, a.coef, a.nmock, a.mstride, a.rowc); break;
+#define X(NN) case NN: cols_n<NN>(a.mode, 0, a.in, outs, 1, 0, tw.get(NN), a.scale, a.amp, s, a.coef, a.nmock, a.mstride, a.rowc); break;
     COLA_FFT_SIZES(X)
 #undef X
     default: break;
@@ -1331,20 +1446,30 @@ void fft_x(const XPassArgs& a, int n, const TwiddleSet& tw, hipStream_t s) {
 
 namespace {
 template <int N>
-void combine_n(const float2* const in[3], float2* out, const CombineSpec& cs, const float* amp,
-               const float2* tw, hipStream_t s) {
-  constexpr int W = fcols_w(N);
-  const ColGeom g = geom(N, W, 0);
-  dim3 grid((unsigned)(g.nchunk * g.nplanes), 1);
-  hipLaunchKernelGGL(k_combine<N>, grid, dim3(fcols_threads(N)), 0, s, in[0], in[1], in[2], out,
-                     g, tw, cs, amp);
+void combine_n(const CombineSpec& cs, float2* out, const float* amp, const float2* tw, hipStream_t s) {
+  const ColGeom g = geom(N, fcols_w(N), 0);
+  hipLaunchKernelGGL(k_combine<N>, dim3((unsigned)(g.nchunk * g.nplanes)), dim3(fcols_threads(N)), 0, s, cs, out, g, tw,
+                     amp);
+}
+template <int N>
+void ycomb_n(const YCombine& yc, float2* out, const float2* tw, hipStream_t s) {
+  const ColGeom g = geom(N, fcols_w(N), 1);
+  hipLaunchKernelGGL(k_ycomb<N>, dim3((unsigned)(g.nchunk * g.nplanes)), dim3(fcols_threads(N)), 0, s, yc, out, g, tw);
 }
 }  // namespace
 
-void fft_combine_x(const float2* const in[3], float2* out, int n, const CombineSpec& cs,
-                   const float* amp, const TwiddleSet& tw, hipStream_t s) {
+void fft_combine_x(const CombineSpec& cs, float2* out, int n, const float* amp, const TwiddleSet& tw, hipStream_t s) {
   switch (n) {
-#define X(NN) case NN: combine_n<NN>(in, out, cs, amp, tw.get(NN), s); break;
+#define X(NN) case NN: combine_n<NN>(cs, out, amp, tw.get(NN), s); break;
+    COLA_FFT_SIZES(X)
+#undef X
+    default: break;
+  }
+}
+
+void fft_combine_y(const YCombine& yc, float2* out, int n, const TwiddleSet& tw, hipStream_t s) {
+  switch (n) {
+#define X(NN) case NN: ycomb_n<NN>(yc, out, tw.get(NN), s); break;
     COLA_FFT_SIZES(X)
 #undef X
     default: break;

@@ -53,3 +53,23 @@ def test_table_sizes(nk):
     ref = fields(32, 64, 100.0, w, (k0, p0))
     got = fields(32, 64, 100.0, w, (k, 1e3 * k ** -1.5))
     assert rel(got["psi1"], ref["psi1"]) < 1e-6 and rel(got["psi2"], ref["psi2"]) < 1e-6
+
+
+@pytest.mark.parametrize("np_side,nm", [(16, 32), (32, 32), (48, 48), (64, 96), (96, 96), (128, 192)])
+def test_initial_condition_adjoint_by_length(np_side, nm):
+    from oracle import adjoint
+    from paper_1507_05329_amd.sim import ColaSim
+    say(f"[gpu] adjoint of the initial conditions {np_side}^3 / {nm}^3")
+    box, t = 3.0 * np_side, bbks_table()
+    w = white_noise(np_side + 1, np_side)
+    d0, p1, p2 = np.random.default_rng(np_side).standard_normal((3, 3, np_side ** 3)).astype(np.float32)
+    sim = ColaSim(np_side, nm, box)
+    try:
+        sim.init_from_noise(torch.from_numpy(w).cuda(), *t)
+        got = sim.init_adjoint(*(torch.from_numpy(x).cuda() for x in (w, d0, p1, p2))).cpu().numpy().astype(np.float64)
+    finally:
+        sim.close()
+    s = box / nm
+    ref = adjoint.ic_adjoint(w.astype(np.float64), box, *t, (p1 + cosmo.growth_D1(0.02, 0.27) * d0) / s,
+                             (p2 + cosmo.growth_D2(0.02, 0.27) * d0) / s)
+    assert rel(got.ravel(), ref.ravel()) < 1e-4
