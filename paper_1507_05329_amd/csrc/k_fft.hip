@@ -43,6 +43,8 @@ constexpr int nstage(int n) { int s = 0; while (radix_at(n, s)) ++s; return s; }
 // staged complex values, 512 from 4096 (measured on the 768 mesh: the row
 // and column passes run 8-18% faster on 512 threads than on 256).
 constexpr int kLdsLimit = 80 * 1024;
+// The last-level cache shared by the chip.
+constexpr long kLastLevelBytes = 256L << 20;
 constexpr int threads_for(int elems) { return elems >= 4096 ? 512 : 256; }
 
 bool make_plan(int n, FftPlan* plan) {
@@ -288,6 +290,21 @@ template <int NT, int TL>
 __device__ __forceinline__ float2 tw_at(const float2* __restrict__ twl, int m) {
   if constexpr (TL == NT) return twl[m];
   else return tw_get<NT>(twl, m);
+}
+// One complex value, nontemporal where NT.
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+template <bool NT>
+__device__ __forceinline__ float2 ld_stream(const float2* p) {
+  if constexpr (NT) {
+    const f32x2 v = __builtin_nontemporal_load(reinterpret_cast<const f32x2*>(p));
+    return make_float2(v.x, v.y);
+  }
+  return *p;
+}
+template <bool NT>
+__device__ __forceinline__ void st_stream(float2* p, float2 v) {
+  if constexpr (NT) __builtin_nontemporal_store(f32x2{v.x, v.y}, reinterpret_cast<f32x2*>(p));
+  else *p = v;
 }
 // a * conj(w)
 __device__ __forceinline__ float2 cmulc(float2 a, float2 w) {
@@ -644,7 +661,15 @@ constexpr int frows_threads_r2c(int n) {
   return n == 2048 ? threads_for(frows_nl_r2c(n) * (n / 2)) : frows_threads(n);
 }
 
-template <int N>
+// Bound by HBM (a read and a write of the mesh in whole lines).  NT:
+// nontemporal loads and stores, for a launch whose meshes fill more than half
+// of the last-level cache, where little of what is written is still there when
+// the y pass reads it.  This pass and the y pass after it, plain -> nontemporal: 1024
+// mesh 1.94 + 1.84 -> 1.59 + 1.86 ms; 768 0.82 + 0.82 -> 0.70 + 0.76 ms; 512
+// 0.230 + 0.243 -> 0.217 + 0.204 ms; 384 (236 MB) 0.100 + 0.108 -> 0.107 +
+// 0.091 ms; a mesh of 256 (75 MB) is read back from the cache, where the
+// nontemporal form of this access pattern is slower (5.8 against 7.8 TB/s).
+template <int N, bool NT>
 __global__ __launch_bounds__(frows_threads_r2c(N), min_waves(frows_threads_r2c(N))) void k_r2c_z(
     float2* __restrict__ mesh, long nrows, int cols, long mesh_stride, const float2* __restrict__ tw,
     long mstride) {
@@ -667,7 +692,7 @@ __global__ __launch_bounds__(frows_threads_r2c(N), min_waves(frows_threads_r2c(N
     const bool in = S0::ok(t) && r0 + l < nrows;
     const float2* p = base + (r0 + l) * cols + j;
 #pragma unroll
-    for (int r = 0; r < S0::R; ++r) v[b][r] = in ? p[r * S0::NBL] : make_float2(0.f, 0.f);
+    for (int r = 0; r < S0::R; ++r) v[b][r] = in ? ld_stream<NT>(p + r * S0::NBL) : make_float2(0.f, 0.f);
   }
   load_twiddles<TL, T>(twl, tw);
   float2 z[SL::KB][SL::R];
@@ -705,7 +730,7 @@ __global__ __launch_bounds__(frows_threads_r2c(N), min_waves(frows_threads_r2c(N
   for (int q = 0; q < KO; ++q) {
     const int i = tid + q * T;
     const int l = i / COLS, k = i - l * COLS;
-    if ((NO % T == 0 || i < NO) && r0 + l < nrows) base[(r0 + l) * cols + k] = xs[q];
+    if ((NO % T == 0 || i < NO) && r0 + l < nrows) st_stream<NT>(base + (r0 + l) * cols + k, xs[q]);
   }
 }
 
@@ -1242,8 +1267,12 @@ void r2c_n(float2* mesh, int nbatch, long mesh_stride, const float2* tw, hipStre
   constexpr int NL = frows_nl_r2c(N), T = frows_threads_r2c(N);
   const long nrows = (long)N * N;
   dim3 grid((unsigned)((nrows + NL - 1) / NL), (unsigned)nbatch, (unsigned)nmock);
-  hipLaunchKernelGGL(k_r2c_z<N>, grid, dim3(T), 0, s, mesh, nrows, (int)(rowc > 0 ? rowc : padded_cols(N)),
-                     mesh_stride, tw, mstride);
+  const int cols = (int)(rowc > 0 ? rowc : padded_cols(N));
+  const long bytes = nrows * (long)padded_cols(N) * (long)sizeof(float2) * nbatch * nmock;
+  if (2 * bytes > kLastLevelBytes)
+    hipLaunchKernelGGL((k_r2c_z<N, true>), grid, dim3(T), 0, s, mesh, nrows, cols, mesh_stride, tw, mstride);
+  else
+    hipLaunchKernelGGL((k_r2c_z<N, false>), grid, dim3(T), 0, s, mesh, nrows, cols, mesh_stride, tw, mstride);
 }
 
 template <int N>
