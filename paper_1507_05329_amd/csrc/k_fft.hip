@@ -256,14 +256,23 @@ constexpr int fcols_ld(int n, int lim = kLdsLimit) {
 // memory idle for long stretches, and wider runs per row cut its HBM
 // transactions (measured at 1024^3/2048^3: 38.9 against 43.9 ms; the
 // one-transform passes are faster on 4 columns).
+// The gradient y pass at 1024 does the same on 16 columns (rows of whole
+// 128-byte lines): 2.93 against 3.40 ms on 8, and the c2r pass that reads its
+// output 5.10 against 5.30 ms.  The Green pass there does not (4.65 against
+// 3.97 ms), nor does any pass at 768 (gradient 1.32 against 1.30, plain
+// inverse 0.85 both, plain forward 0.77 against 0.76 ms).
 constexpr int kWideLds = 156 * 1024;
-constexpr int cols_lim(int n, int mode) { return (mode == X_FWD_GREEN && n == 2048) ? kWideLds : kLdsLimit; }
+constexpr int cols_lim(int n, int mode) {
+  return (mode == X_FWD_GREEN && n == 2048) || (mode == X_INV_GRAD_YZ && n == 1024) ? kWideLds : kLdsLimit;
+}
 static_assert(fcols_w(2048) * fcols_ld(2048) * 8 + ftw_len(2048) * 8 <= kLdsLimit, "column-pass LDS");
 static_assert(fcols_w(512) * fcols_ld(512) * 8 + ftw_len(512) * 8 <= kLdsLimit, "column-pass LDS");
 static_assert(fcols_w(1024) * fcols_ld(1024) * 8 + ftw_len(1024) * 8 <= kLdsLimit, "column-pass LDS");
 static_assert(fcols_w(2048, kWideLds) == 8 && fcols_threads(2048, kWideLds) == 1024 &&
                   8 * fcols_ld(2048, kWideLds) * 8 + ftw_len(2048, kWideLds) * 8 <= kWideLds,
               "wide Green pass LDS");
+static_assert(fcols_w(1024, kWideLds) == 16 && 16 * fcols_ld(1024, kWideLds) * 8 + ftw_len(1024, kWideLds) * 8 <= kWideLds,
+              "wide gradient pass LDS");
 
 // Waves per SIMD the register budget must allow: two 1024-thread workgroups per CU.
 constexpr int min_waves(int t) { return t >= 1024 ? 8 : 4; }
@@ -1317,9 +1326,9 @@ template <int N>
 void cols_n(int mode, int axis, const float2* in, float2* const out[3], int nbatch, long mesh_stride,
             const float2* tw, float scale, const float* amp, hipStream_t s,
             const StepCoef* coef = nullptr, int nmock = 1, long mstride = 0, long rowc = 0) {
-  constexpr int LG = cols_lim(N, X_FWD_GREEN);
-  const int W = mode == X_FWD_GREEN ? fcols_w(N, LG) : fcols_w(N);
-  const int T = mode == X_FWD_GREEN ? fcols_threads(N, LG) : fcols_threads(N);
+  constexpr int WN = fcols_w(N), WW = fcols_w(N, kWideLds), TN = fcols_threads(N), TW = fcols_threads(N, kWideLds);
+  const bool wide = cols_lim(N, mode) > kLdsLimit;
+  const int W = wide ? WW : WN, T = wide ? TW : TN;
   ColGeom g = geom(N, W, axis, rowc);
   // The Green pass takes only the column blocks that hold a frequency
   // 0 .. N/2 (the rest of a padded row is never read; the passes after it
