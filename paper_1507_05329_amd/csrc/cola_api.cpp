@@ -909,13 +909,59 @@ int cola_pk_of(cola_ctx* c, const float* disp, int32_t ng, const double* edges, 
   return pk_of(c, disp, ng, edges, nbins, kmean, pk, nmodes);
 }
 
+namespace {
+// True if [p, p + bytes) lies in one allocation of the current device (the
+// kernel may read or write it; another device's or the host's memory, and a
+// range that the runtime refuses, are left to hipMemcpyAsync).
+bool device_range(const void* p, size_t bytes) {
+  hipPointerAttribute_t at;
+  hipDeviceptr_t base = nullptr;
+  size_t size = 0;
+  int dev = -1;
+  if (reinterpret_cast<uintptr_t>(p) % sizeof(float) || hipGetDevice(&dev) != hipSuccess) return false;
+  if (hipPointerGetAttributes(&at, p) != hipSuccess ||
+      hipMemGetAddressRange(&base, &size, const_cast<void*>(p)) != hipSuccess) {
+    (void)hipGetLastError();
+    return false;
+  }
+  return at.type == hipMemoryTypeDevice && at.device == dev &&
+         static_cast<const char*>(p) + bytes <= static_cast<const char*>(base) + size;
+}
+
+// Copies of n floats each, in order where a source overlaps a destination.
+int copy_arrays(cola_ctx* c, const CopySet& a, long n) {
+  const size_t b = n * sizeof(float);
+  bool one = a.count > 0;
+  for (int i = 0; i < a.count && one; ++i) {
+    one = device_range(a.dst[i], b) && device_range(a.src[i], b);
+    for (int j = 0; j < a.count && one; ++j) {
+      const uintptr_t s = reinterpret_cast<uintptr_t>(a.src[j]), d = reinterpret_cast<uintptr_t>(a.dst[i]);
+      const uintptr_t e = reinterpret_cast<uintptr_t>(a.dst[j]);
+      one = (s + b <= d || d + b <= s) && (i == j || e + b <= d || d + b <= e);
+    }
+  }
+  if (one) {
+    launch_copy_arrays(a, n, c->stream);
+    LAUNCH_CHECK(c, "copy_arrays");
+    return COLA_OK;
+  }
+  for (int i = 0; i < a.count; ++i)
+    HIP_TRY(c, hipMemcpyAsync(a.dst[i], a.src[i], b, hipMemcpyDeviceToDevice, c->stream));
+  return COLA_OK;
+}
+}  // namespace
+
 int cola_get_state(cola_ctx* c, float* d, float* v, float* p1, float* p2, double* ax, double* av) {
   if (!c) return COLA_EINVAL;
-  const size_t b = 3 * c->np3 * sizeof(float);
-  if (d) HIP_TRY(c, hipMemcpyAsync(d, c->disp, b, hipMemcpyDeviceToDevice, c->stream));
-  if (v) HIP_TRY(c, hipMemcpyAsync(v, c->vres, b, hipMemcpyDeviceToDevice, c->stream));
-  if (p1) HIP_TRY(c, hipMemcpyAsync(p1, c->psi1, b, hipMemcpyDeviceToDevice, c->stream));
-  if (p2) HIP_TRY(c, hipMemcpyAsync(p2, c->psi2, b, hipMemcpyDeviceToDevice, c->stream));
+  float* user[4] = {d, v, p1, p2};
+  float* own[4] = {c->disp, c->vres, c->psi1, c->psi2};
+  CopySet set;
+  for (int i = 0; i < 4; ++i)
+    if (user[i]) {
+      set.dst[set.count] = user[i];
+      set.src[set.count++] = own[i];
+    }
+  if (int rc = copy_arrays(c, set, 3 * c->np3)) return rc;
   if (ax) *ax = c->a_x;
   if (av) *av = c->a_v;
   return COLA_OK;
@@ -927,11 +973,15 @@ int cola_set_state(cola_ctx* c, const float* d, const float* v, const float* p1,
   if (!(ax > 0) || !(av > 0)) return fail(c, COLA_EINVAL, "scale factors must be positive");
   if (!c->have_state && (!d || !v || !p1 || !p2))
     return fail(c, COLA_ESTATE, "first set_state must provide every array");
-  const size_t b = 3 * c->np3 * sizeof(float);
-  if (d) HIP_TRY(c, hipMemcpyAsync(c->disp, d, b, hipMemcpyDeviceToDevice, c->stream));
-  if (v) HIP_TRY(c, hipMemcpyAsync(c->vres, v, b, hipMemcpyDeviceToDevice, c->stream));
-  if (p1) HIP_TRY(c, hipMemcpyAsync(c->psi1, p1, b, hipMemcpyDeviceToDevice, c->stream));
-  if (p2) HIP_TRY(c, hipMemcpyAsync(c->psi2, p2, b, hipMemcpyDeviceToDevice, c->stream));
+  const float* user[4] = {d, v, p1, p2};
+  float* own[4] = {c->disp, c->vres, c->psi1, c->psi2};
+  CopySet set;
+  for (int i = 0; i < 4; ++i)
+    if (user[i]) {
+      set.dst[set.count] = own[i];
+      set.src[set.count++] = user[i];
+    }
+  if (int rc = copy_arrays(c, set, 3 * c->np3)) return rc;
   c->a_x = ax;
   c->a_v = av;
   c->have_state = true;

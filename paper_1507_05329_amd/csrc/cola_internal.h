@@ -27,6 +27,8 @@ bool fft_size_supported(int n);   // transform sizes with compiled kernels
 int fft_block_order(int n, int kind);
 int set_fft_block_order(int n, int kind, int order);
 
+// The last-level cache shared by the chip.
+constexpr long kLastLevelBytes = 256L << 20;
 // Padded complex row length of an n^3 real mesh in the r2c layout: the
 // (n/2+1) half-spectrum rounded up to 16 complex values (128-byte rows).
 inline long padded_cols(int n) { return ((long)(n / 2 + 1) + 15) / 16 * 16; }
@@ -271,6 +273,14 @@ void launch_axpy_to_mesh(const float* a, const float* b, float alpha, int n, flo
                          long row_stride, long mesh_stride_floats, hipStream_t s);
 void launch_pk_adj_modes(const float2* X, float2* Z, int ng, double box, const double* edges,
                          int nbins, const double* cbar, const double* sums, hipStream_t s);
+// Up to 4 array copies of n floats each in one launch (device ranges of this
+// GPU, no source overlapping a destination).
+struct CopySet {
+  int count = 0;
+  float* dst[4];
+  const float* src[4];
+};
+void launch_copy_arrays(const CopySet& a, long n, hipStream_t s);
 // Non-finite check.
 void launch_check_finite(const float* x, long n, uint32_t* flag, hipStream_t s);
 

@@ -43,8 +43,6 @@ constexpr int nstage(int n) { int s = 0; while (radix_at(n, s)) ++s; return s; }
 // staged complex values, 512 from 4096 (measured on the 768 mesh: the row
 // and column passes run 8-18% faster on 512 threads than on 256).
 constexpr int kLdsLimit = 80 * 1024;
-// The last-level cache shared by the chip.
-constexpr long kLastLevelBytes = 256L << 20;
 constexpr int threads_for(int elems) { return elems >= 4096 ? 512 : 256; }
 
 bool make_plan(int n, FftPlan* plan) {
