@@ -49,13 +49,16 @@ double integrate(const F& f, double a, double b, double rtol, int depth = 0) {
   return integrate(f, a, m, rtol, depth + 1) + integrate(f, m, b, rtol, depth + 1);
 }
 
+// int_0^a dx / (x E)^3 in s = sqrt(x): the integrand x^(3/2) / (Om + OL x^3)^(3/2)
+// has no derivatives at 0, 2 s^4 / (Om + OL s^6)^(3/2) is analytic there (in x,
+// bisection runs into that end).  The scalars of a step, eight of these
+// integrals: 112 us of host time in x, 8 us in s.
 double heath(double a, double om) {
-  auto f = [om](double x) {
-    if (x <= 0) return 0.0;
-    const double ae = x * hubble_E(x, om);
-    return 1.0 / (ae * ae * ae);
+  auto f = [om](double s) {
+    const double s2 = s * s, g = om + (1.0 - om) * s2 * s2 * s2;
+    return 2.0 * s2 * s2 / (g * std::sqrt(g));
   };
-  return 2.5 * om * hubble_E(a, om) * integrate(f, 0.0, a, 1e-14);
+  return 2.5 * om * hubble_E(a, om) * integrate(f, 0.0, std::sqrt(a), 1e-14);
 }
 
 }  // namespace
