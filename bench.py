@@ -66,8 +66,8 @@ def stage_bytes(np_side: int, nm: int) -> dict:
     R = 4 * M                               # real float32 mesh
     C = 8 * nm * nm * (nm // 2 + 1)         # complex half mesh
     return {
-        "sort": 32 * n_p,                   # read d (12), write+read key/rank (16), write perm (4)
-        "deposit": 16 * n_p + R,            # read perm + d, write delta
+        "sort": 32 * n_p,                   # read d (12), write a record (16) and an id (4)
+        "deposit": 16 * n_p + R,            # read the records, write delta
         "fft_z": R + C,                     # real in, half spectrum out
         "fft_y": 2 * C,
         "fft_x_green": 3 * C,               # 1 read, 2 writes (IDFT_x of i k_x phi and of phi)

@@ -128,9 +128,8 @@ int cola_step(cola_ctx* ctx, double a0, double a1);
 
 /* Density contrast delta = rho/rho_bar - 1 of the current positions on the
  * nmesh^3 mesh by the deterministic CIC deposit (Sec. 3.3 CIC), written to
- * dev_out (nmesh^3 float32, C order).  Bitwise reproducible: per cell the
- * weights are summed in ascending particle id, nodes add their 8 source
- * cells in a fixed order. */
+ * dev_out (nmesh^3 float32, C order).  Bitwise reproducible: a node's
+ * weights are summed exactly, as 64-bit fixed-point integers. */
 int cola_density(cola_ctx* ctx, float* dev_out);
 
 /* For callers that cannot allocate device memory (code under HIP graph
