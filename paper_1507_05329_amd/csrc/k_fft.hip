@@ -549,11 +549,12 @@ __global__ __launch_bounds__(fcols_threads(N, cols_lim(N, MODE)), 4) void k_cols
         const int e = st_elem<SL, T>(tid, b, r, c);
         const int nx = signed_freq(e, N), nz = c0 + c;
         const int n2 = nx * nx + pfreq * pfreq + nz * nz;
-        // hardware reciprocal (within 1 ulp): one instruction instead of a division
         bool zero = n2 == 0 || nz > N / 2;
         if constexpr (MODE == X_FWD_PHI2)
           zero = zero || nx == N / 2 || nx == -N / 2 || pfreq == N / 2 || pfreq == -N / 2 || nz == N / 2;
-        const float inv = zero ? 0.f : scale * __builtin_amdgcn_rcpf((float)n2);
+        // step: hardware reciprocal (within 1 ulp), one instruction instead of a
+        // division; initial conditions: one correctly rounded quotient
+        const float inv = zero ? 0.f : MODE == X_FWD_PHI2 ? scale / (float)n2 : scale * __builtin_amdgcn_rcpf((float)n2);
         f[b][r] = make_float2(inv * f[b][r].x, inv * f[b][r].y);
         const float kx = (nx == N / 2 || nx == -N / 2) ? 0.f : (float)nx;
         u[b][r] = make_float2(-kx * f[b][r].y, kx * f[b][r].x);  // i n_x phi
@@ -576,7 +577,7 @@ __global__ __launch_bounds__(fcols_threads(N, cols_lim(N, MODE)), 4) void k_cols
         int c;
         const int nx = signed_freq(st_elem<S0, T>(tid, b, r, c), N), nz = c0 + c;
         const int n2 = nx * nx + pfreq * pfreq + nz * nz;
-        const float inv = (n2 == 0 || nz > N / 2) ? 0.f : scale * __builtin_amdgcn_rcpf((float)n2);
+        const float inv = (n2 == 0 || nz > N / 2) ? 0.f : scale / (float)n2;   // correctly rounded
         v[b][r] = make_float2(inv * v[b][r].x, inv * v[b][r].y);
       }
     constexpr int M = MODE == X_PHI2 ? 2 : 3;
