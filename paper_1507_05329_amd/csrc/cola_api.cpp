@@ -1203,7 +1203,10 @@ int cola_init_2lpt_adjoint(cola_ctx* c, const float* noise, const float* dbar0, 
   divergence_xy(c, A, 2 * ms, np, -sgrad, &ws);
   fft_combine_x(ws, S, np, c->amp, c->tw, c->stream);
   fft_y(S, np, 1, 0, 1, c->tw, c->stream);
-  fft_c2r_z(S, np, 1, 0, c->tw, c->stream, noise_bar);
+  // the z pass writes pairs of floats: straight into noise_bar where it is aligned for them
+  const bool pairs = reinterpret_cast<uintptr_t>(noise_bar) % sizeof(float2) == 0;
+  fft_c2r_z(S, np, 1, 0, c->tw, c->stream, pairs ? noise_bar : nullptr);
+  if (!pairs) launch_copy_from_mesh(reinterpret_cast<float*>(S), np, rs, noise_bar, 1.0f, c->stream);
   LAUNCH_CHECK(c, "cola_init_2lpt_adjoint");
   return COLA_OK;
 }
