@@ -166,7 +166,7 @@ __global__ __launch_bounds__(T) void k_deposit_mass(const float2* __restrict__ f
       if (x0 + g * T + threadIdx.x < s1) {
         const float f[3] = {a[g].x, a[g].y, b[g].x};
         const uint32_t c = __float_as_uint(b[g].y);
-        add_mass(sh, f, (int)(((c >> 8) * kAcc + ((c >> 4) & 15)) * kAcc + (c & 15)), 0);
+        add_mass(sh, f, (int)((((c >> 8) & 15) * kAcc + ((c >> 4) & 15)) * kAcc + (c & 15)), 0);
       }
     }
   }
@@ -182,7 +182,7 @@ __global__ __launch_bounds__(T) void k_deposit_mass(const float2* __restrict__ f
     if (x < total) {
       const float f[3] = {ba.x, ba.y, bb.x};
       const uint32_t c = __float_as_uint(bb.y);
-      const int lx = nb & 4 ? -1 : (int)(c >> 8), ly = nb & 2 ? -1 : (int)((c >> 4) & 15),
+      const int lx = nb & 4 ? -1 : (int)((c >> 8) & 15), ly = nb & 2 ? -1 : (int)((c >> 4) & 15),
                 lz = nb & 1 ? -1 : (int)(c & 15);
       add_mass(sh, f, (lx * kAcc + ly) * kAcc + lz, nb);
     }
@@ -271,7 +271,7 @@ __global__ __launch_bounds__(T) void k_deposit_weighted(const float* __restrict_
   const Boundary bd(off, tx, ty, tz, nt);
   const uint32_t total = bd.total;
   auto fetch = [&](Part& p, uint32_t place, int nb, int c0, int c1) {
-    const uint32_t id = perm[place];
+    const uint32_t id = min(perm[place], (uint32_t)np3 - 1u);
     const float dv[3] = {disp[id], disp[np3 + id], disp[2 * np3 + id]};
 #pragma unroll
     for (int q = 0; q < NC; ++q)

@@ -5,7 +5,10 @@
 //
 // Two passes over the displacements: the first counts, the second (after the
 // scan) finds each particle's place again and writes what the deposit reads
-// there, so nothing per particle is kept between them.  A workgroup of either
+// there, so nothing per particle is kept between them.  Displacements that
+// another stream changes between the two get a wrong place, but none outside the
+// arrays (the deposits take whatever lies at a place as a valid cell and id).  A
+// workgroup of either
 // pass takes 1024 particles, four per thread with all loads issued first, and
 // counts them by bucket in an LDS table, so that its chain of dependent
 // requests (positions, table, one global atomic per bucket) is paid once per
@@ -136,6 +139,7 @@ __global__ __launch_bounds__(256) void k_tile_fill(const float* __restrict__ dis
 #pragma unroll
   for (int u = 0; u < kPer; ++u) {
     const uint32_t p = h.cnt[slot[u]] + rank[u];
+    if (p >= (uint32_t)np3) continue;   // only if the displacements changed since the count
     if constexpr (REC) {
       fxy[p] = make_float2(d[u][0], d[u][1]);
       fzc[p] = make_float2(d[u][2], __uint_as_float(cell[u]));
