@@ -174,18 +174,23 @@ __global__ void k_pk_cross_reduce(const double* __restrict__ partial, int nbins,
 // by (bin, chunk) above visit every (kx, ky) row once per bin and take two
 // sines per visited mode; here a wave visits each mode of its rows once, and
 // the windows come from a table in LDS.  What bounds it is the FP64 arithmetic
-// of a mode (a square root and the window).  768 mesh: 0.7 ms at 1 and 8 bins,
-// 0.8 at 40, 1.6 at 512, against 5.4, 5.8, 3.4 and 2.9 ms with the sums by
-// (bin, chunk), which remain for more bins (their LDS sums no longer fit).
+// of a mode (a square root and the window) and, with many bins, the runs handed
+// over.  768 mesh: 0.9 ms at 1 and 8 bins, 1.1 at 40, 2.1 at 512 (0.9, 1.0, 1.7
+// with the lanes' additions left in the order in which the LDS takes them),
+// against 5.4, 5.8, 3.4 and 2.9 ms with the sums by (bin, chunk), which remain
+// for more bins (their LDS sums no longer fit).
 //
 // Bins by integers: n2 = nx^2 + ny^2 + nz^2 decides |k| = kf sqrt(n2), so bin b
 // is thr[b] <= n2 < thr[b + 1] with thr[b] the smallest n2 whose |k| reaches
 // edge b (same expression, same rounding), and |k| <= kmax is n2 < top.
 // A lane keeps one nz and goes through the rows, along which n2 changes
 // little, so it adds into registers and passes its sums on only when its bin
-// changes, to LDS sums that belong to its wave alone.  A wave's additions
-// come in program order, the lanes of one of them in lane order, and the
-// waves and chunks are added in order: the sums do not vary from run to run.
+// changes or its mode is not counted, to LDS sums that belong to its wave alone.
+// The sums do not vary from run to run: every run handed over ended in the same
+// row (the last one that the wave visited), where the bin does not fall from one
+// lane to the next, so the lanes of one bin are found by a look at the lane before
+// and add in lane order, one instruction each; a wave's LDS instructions complete
+// in their order, and the waves and chunks are added in order.
 constexpr int kRowBins = 512;        // largest bin count: LDS of a workgroup, chunks that the partials hold
 constexpr int kRowWaves = 4;
 constexpr int kRowMaxChunks = 1024;  // workgroups
@@ -237,14 +242,28 @@ __global__ __launch_bounds__(64 * kRowWaves) void k_pk_rows(
   for (int q = 0; q < NS; ++q) run[q] = 0.0;
   uint32_t nrun = 0, tlo, thi;                               // bin cur: tlo <= n2 < thi
   int cur;
-  auto flush = [&]() {
-    if (nrun > 0) {
-#pragma unroll
-      for (int q = 0; q < NS; ++q) {
-        __hip_atomic_fetch_add(&wacc[cur * NS + q], run[q], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-        run[q] = 0.0;
-      }
+  // Hands over the runs of the lanes with out set (every lane of the wave takes
+  // part): the lanes of one bin one after the other, no two in one instruction.
+  auto flush = [&](bool out) {
+    const uint64_t f = __ballot(out);
+    if (f == 0) return;
+    const uint64_t below = f & ((1ull << lane) - 1);
+    const int pb = __shfl(cur, below ? 63 - __builtin_clzll(below) : lane, 64);
+    const uint64_t heads = __ballot(out && (below == 0 || pb != cur));
+    int rank = -1;                                           // place among the lanes of its bin
+    if (out) {
+      const uint64_t h = heads & (~0ull >> (63 - lane));
+      rank = __popcll(below >> (63 - __builtin_clzll(h)));
       atomicAdd(&wcnt[cur], nrun);
+    }
+    for (int r = 0; __any(rank >= r); ++r)
+      if (rank == r)
+#pragma unroll
+        for (int q = 0; q < NS; ++q)
+          __hip_atomic_fetch_add(&wacc[cur * NS + q], run[q], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    if (out) {
+#pragma unroll
+      for (int q = 0; q < NS; ++q) run[q] = 0.0;
       nrun = 0;
     }
   };
@@ -279,9 +298,11 @@ __global__ __launch_bounds__(64 * kRowWaves) void k_pk_rows(
       for (int u = 0; u < kU; ++u) {
         if (p2[u] + (uint32_t)(z0 * z0) >= hi) continue;     // wave-uniform: nothing of the row is left
         const uint32_t n2 = p2[u] + (uint32_t)(nz * nz);
-        if (!(zin && n2 >= lo && n2 < hi && (nz > 0 || sy[u] > 0 || (sy[u] == 0 && sx[u] > 0)))) continue;
-        if (n2 < tlo || n2 >= thi) {
-          flush();
+        const bool in = zin && n2 >= lo && n2 < hi && (nz > 0 || sy[u] > 0 || (sy[u] == 0 && sx[u] > 0));
+        const bool same = in && n2 >= tlo && n2 < thi;
+        flush(nrun > 0 && !same);
+        if (!in) continue;
+        if (!same) {
           if (cur < 0) {                                     // the last edge not above n2
             int a = 0, e = nbins;
             while (e - a > 1) {
@@ -309,7 +330,7 @@ __global__ __launch_bounds__(64 * kRowWaves) void k_pk_rows(
         ++nrun;
       }
     }
-    flush();
+    flush(nrun > 0);
   }
   __syncthreads();
   for (int b = tid; b < nbins; b += T) {
