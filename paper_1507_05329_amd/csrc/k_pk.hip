@@ -3,9 +3,10 @@
 // delta_k = (V / Ng^3) DFT[delta] / W_CIC(k), W_CIC = prod sinc^2(pi n_e / Ng),
 // averaged per |k| bin with the mean |k|.  Only |k| <= pi Ng / L is used.
 //
-// Up to 512 bins: k_pk_rows below.  More bins: workgroup (bin b, chunk c)
-// visits the (kx, ky) rows of chunk c; a thread walks one row's kz range that can fall in bin b
-// (found analytically, each mode then tested exactly), accumulating in FP64
+// Up to 512 bins (density / momentum spectra: what 64 KB of LDS hold, 441 at
+// side 32 and 387 at 2048): k_pk_rows below.  More bins: workgroup (bin b, chunk
+// c) visits the (kx, ky) rows of chunk c; a thread walks one row's kz range that
+// can fall in bin b (found analytically, each mode then tested exactly), accumulating in FP64
 // in a fixed order; the workgroup sums its threads by a fixed tree, and a
 // second kernel sums the chunks in order.
 #include "cola_device.h"
@@ -170,7 +171,7 @@ __global__ void k_pk_cross_reduce(const double* __restrict__ partial, int nbins,
 }
 
 // ---------------------------------------------------------------------------
-// Spectra of few bins (kRowBins at most), one pass over the modes.  The sums
+// Spectra of few bins (pk_rows_plan), one pass over the modes.  The sums
 // by (bin, chunk) above visit every (kx, ky) row once per bin and take two
 // sines per visited mode; here a wave visits each mode of its rows once, and
 // the windows come from a table in LDS.  What bounds it is the FP64 arithmetic
