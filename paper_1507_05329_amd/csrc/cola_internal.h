@@ -228,7 +228,6 @@ void launch_copy_from_mesh(const float* mesh, int n, long row_stride, float* dst
                            hipStream_t s, int elem = 1);
 void launch_init_particles(float* disp, float* vres, const float* psi1, const float* psi2,
                            long np3, float D1, float D2, hipStream_t s);
-void launch_axpby(float* y, const float* x, float a, float b, long n, hipStream_t s);
 // Power spectrum binning (k_pk.hip).
 // partial: kPkPartialDoubles doubles; out: sum |k|, sum P and the count per bin.
 constexpr int kPkMaxBins = 4096, kPkChunks = 64;

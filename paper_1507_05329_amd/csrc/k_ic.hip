@@ -130,14 +130,4 @@ void launch_init_particles(float* disp, float* vres, const float* psi1, const fl
                      psi1, psi2, n, D1, D2);
 }
 
-__global__ void k_axpby(float* __restrict__ y, const float* __restrict__ x, float a, float b, long n) {
-  for (long i = blockIdx.x * (long)blockDim.x + threadIdx.x; i < n;
-       i += (long)gridDim.x * blockDim.x)
-    y[i] = a * y[i] + b * x[i];
-}
-
-void launch_axpby(float* y, const float* x, float a, float b, long n, hipStream_t s) {
-  hipLaunchKernelGGL(k_axpby, dim3(grid_1d(n)), dim3(256), 0, s, y, x, a, b, n);
-}
-
 }  // namespace cola
