@@ -66,7 +66,7 @@ def stage_bytes(np_side: int, nm: int) -> dict:
     R = 4 * M                               # real float32 mesh
     C = 8 * nm * nm * (nm // 2 + 1)         # complex half mesh
     return {
-        "sort": 32 * n_p,                   # read d (12), write a record (16) and an id (4)
+        "sort": 32 * n_p,                   # read d (12), write a record (16); 4 for the id that the adjoint's sort adds
         "deposit": 16 * n_p + R,            # read the records, write delta
         "fft_z": R + C,                     # real in, half spectrum out
         "fft_y": 2 * C,

@@ -69,7 +69,7 @@ int validate(const cola_params* p) {
     return COLA_EINVAL;
   if (!fft_size_supported(p->np)) return COLA_EUNSUPPORTED;
   if (p->nmesh % 8 != 0 || !fft_size_supported(p->nmesh) || p->nmesh < p->np) return COLA_EUNSUPPORTED;
-  // particle ids fill 30 bits of the deposit's sort keys: at most 2^30 particles
+  // home cells divide ids by multiply-shift, exact below 2^30 (lat_div): at most 2^30 particles
   if ((long)p->np * p->np * p->np > (1L << 30)) return COLA_EUNSUPPORTED;
   return COLA_OK;
 }

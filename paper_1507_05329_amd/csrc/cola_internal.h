@@ -305,8 +305,8 @@ struct cola_ctx {
   uint32_t* offsets = nullptr;  // nbucket + 1
   uint32_t* scan_scratch = nullptr;
   long nbucket = 0;
-  // mesh region: 3 padded complex half meshes of nmesh (PM step), also
-  // carved into 4 meshes of np for the initial conditions
+  // mesh region: 3 padded complex half meshes of nmesh (PM step), also carved
+  // into meshes of np: 6 for the initial conditions, 7 for their adjoint
   float2* meshbase = nullptr;
   float2* mesh[3] = {nullptr, nullptr, nullptr};
   long mesh_stride = 0;         // complex values per PM mesh

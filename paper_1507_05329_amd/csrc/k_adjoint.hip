@@ -1,6 +1,6 @@
 // Reverse-mode kernels of the COLA step (Koda et al. 2015, Sec. 2.2, eqs.
-// cola-kick and cola-drift with the PM force), of the density and P(k)
-// outputs (Sec. 3.3) and of the 2LPT source term (Sec. 2.1).
+// cola-kick and cola-drift with the PM force) and of the density output (Sec.
+// 3.3); those of P(k) are in k_pk.hip, of the 2LPT source (Sec. 2.1) in k_fft.hip.
 //
 // Step, per particle (mesh units, x = q + d at the step start):
 //   vt = vbar' + I dbar';  Psi1bar += e1 dbar' - c1 vt;  Psi2bar += e2 dbar' - c2 vt

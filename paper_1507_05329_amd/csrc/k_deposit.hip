@@ -20,12 +20,17 @@
 // whose unit follows from the largest weight of the component (k_weight_max)
 // and the number of particles in the region, so a node's sum is exact but for
 // the rounding of each product to at least 2^-50 of that weight (2^-43 where a
-// region holds 2^19 particles), and again does not depend on any order.
+// region holds 2^19 particles), and again does not depend on any order.  A node
+// that only weights 2^-27 of the largest or less reach holds fewer bits than a
+// float; every user transforms the mesh in float32 next, whose rounding, some
+// 2^-24 of a mode that holds the largest weight, lies above what is left out
+// there.
 #include "cola_device.h"
 #include "cola_internal.h"
 
-// Every float operation in this file is a single IEEE rounding (the
-// deterministic order is part of the result): no fused multiply-add.
+// Every float operation in this file is a single IEEE rounding (the order is
+// part of the result): no fused multiply-add but the one that is written, which
+// rounds an exact product to a whole number of units.
 #pragma clang fp contract(off)
 
 namespace cola {

@@ -256,9 +256,13 @@ constexpr int fcols_ld(int n, int lim = kLdsLimit) {
 // one-transform passes are faster on 4 columns).
 // The gradient y pass at 1024 does the same on 16 columns (rows of whole
 // 128-byte lines): 2.93 against 3.40 ms on 8, and the c2r pass that reads its
-// output 5.10 against 5.30 ms.  The Green pass there does not (4.65 against
-// 3.97 ms), nor does any pass at 768 (gradient 1.32 against 1.30, plain
-// inverse 0.85 both, plain forward 0.77 against 0.76 ms).
+// output 5.10 against 5.30 ms.  Lengths are named one by one because no size
+// decides: 768 has the same 16 columns and whole lines in 156 KB and gains
+// nothing (gradient 1.32 against 1.30, plain inverse 0.85 both, plain forward
+// 0.77 against 0.76, Green 1.93 against 1.70 ms), the Green pass at 1024 loses
+// (4.57 against 3.93 ms), and at 1536, where the wide form has 8 columns instead
+// of 4, both lose (gradient 12.8 against 10.7, Green 19.3 against 18.5 ms), as
+// the gradient does at 2048 (24.4 against 23.3 ms).
 constexpr int kWideLds = 156 * 1024;
 constexpr int cols_lim(int n, int mode) {
   return (mode == X_FWD_GREEN && n == 2048) || (mode == X_INV_GRAD_YZ && n == 1024) ? kWideLds : kLdsLimit;

@@ -1,5 +1,5 @@
-// Initial-condition kernels: white noise, copies between particle arrays and
-// padded meshes, the 2LPT source term and the initial particle state
+// Initial-condition kernels: white noise, the amplitude table, copies between
+// particle arrays and padded meshes, and the initial particle state
 // (Koda et al. 2015, Sec. 2.1: x = q + D1 Psi1 + D2 Psi2; Sec. 2.3: Gaussian
 // initial random modes).
 #include "cola_device.h"

@@ -1,7 +1,6 @@
 // Tile sort for the deterministic CIC deposit: bucket = (16^3 tile of the home
 // cell, face class).  Integer atomics only; the order inside a bucket is
-// arbitrary (the mass deposit does not depend on it, the weighted one orders
-// particles by id itself).
+// arbitrary (both deposits add integers and do not depend on it).
 //
 // Two passes over the displacements: the first counts, the second (after the
 // scan) finds each particle's place again and writes what the deposit reads
