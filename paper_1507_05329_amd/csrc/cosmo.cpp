@@ -52,13 +52,13 @@ double integrate(const F& f, double a, double b, double rtol, int depth = 0) {
 
 // int_0^a dx / (x E)^3 in s = sqrt(x): the integrand x^(3/2) / (Om + OL x^3)^(3/2)
 // has no derivatives at 0, 2 s^4 / (Om + OL s^6)^(3/2) is analytic there (in x,
-// bisection runs into that end).  Written as 2 s / (Om / s^2 + OL s^4)^(3/2) it
-// overflows to 0 at both ends instead of to a quotient of infinities.  The scalars of a step, eight of these
+// bisection runs into that end).  Past a = 1e100 it is below every double, and
+// its factors overflow.  The scalars of a step, eight of these
 // integrals: 112 us of host time in x, 8 us in s.
 double heath(double a, double om) {
   auto f = [om](double s) {
-    const double s2 = s * s, g = om / s2 + (1.0 - om) * s2 * s2;
-    return 2.0 * s / (g * std::sqrt(g));
+    const double s2 = s * s, g = om + (1.0 - om) * s2 * s2 * s2;
+    return g >= 1e300 ? 0.0 : 2.0 * s2 * s2 / (g * std::sqrt(g));
   };
   return 2.5 * om * hubble_E(a, om) * integrate(f, 0.0, std::sqrt(a), 1e-14);
 }
