@@ -137,8 +137,7 @@ __global__ __launch_bounds__(256) void k_tile_fill(const float* __restrict__ dis
   if constexpr (PERM) perm = mock_ptr(perm, mstride);
 #pragma unroll
   for (int u = 0; u < kPer; ++u) {
-    const uint32_t p = h.cnt[slot[u]] + rank[u];
-    if (p >= (uint32_t)np3) continue;   // only if the displacements changed since the count
+    const uint32_t p = min(h.cnt[slot[u]] + rank[u], (uint32_t)np3 - 1u);   // past it if the displacements changed
     if constexpr (REC) {
       fxy[p] = make_float2(d[u][0], d[u][1]);
       fzc[p] = make_float2(d[u][2], __uint_as_float(cell[u]));
